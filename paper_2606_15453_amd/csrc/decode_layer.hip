@@ -22,7 +22,11 @@ namespace stmoe {
 int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
                int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
                float* y, void* ws, hipStream_t s, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride);
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready);
+bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype);
+int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
+                   const void* const* eptr, const void* const* sptr, int n_shared, void* ws, const void* ebase,
+                   size_t estride, hipStream_t st);
 int route_logits(const void* x, const void* w_gate, int B, int H, int E, int dtype, float* z, hipStream_t s);
 size_t update_predict_seq_bytes(int L);
 int update_predict_seq_args(stmoe_predictor* p, const int32_t* idx_all, void* dev_args);
@@ -445,7 +449,11 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         STMOE_HIP(hipStreamWaitEvent(c->s, c->ev_side, 0));
         c->side_pending = false;
     }
+    const bool takes_plan = !c->cache && ffn_takes_plan(B, K, c->H, c->I, E, c->n_shared, c->dtype);
     const bool route_in_ffn = !c->cache && B * E <= kRouteInFfnMax;
+    const bool plan = takes_plan && !route_in_ffn;
+    const void* ebase = c->rbase.empty() ? nullptr : c->rbase[size_t(layer)];
+    const void* const* sptr = c->n_shared ? c->shared + size_t(layer) * c->n_shared : nullptr;
     float* zbuf = reinterpret_cast<float*>(c->route_ws);
     const bool timed = timing && timed_token(c, token);
     moe_ctx::TimedLayer tl;
@@ -463,11 +471,19 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         if (int rc = stamp_event(tl.route0, c->s)) return rc;
     if (route_in_ffn) {
         if (int rc = route_logits(x, c->router[layer], B, c->H, E, c->dtype, zbuf, c->s)) return rc;
-    } else if (use && c->side) {
-        if (int rc = moe_route_topk(x, c->router[layer], B, c->H, E, K, c->dtype, c->renorm, idx_l, w_l,
-                                    nullptr, c->route_ws, c->route_ws_bytes, c->s))
+    } else if (plan || (use && c->side)) {
+        if (plan) {
+            // the tail launch also builds the FFN's slot plan
+            if (int rc = route_logits(x, c->router[layer], B, c->H, E, c->dtype, zbuf, c->s)) return rc;
+            if (int rc = ffn_route_plan(zbuf, c->renorm, idx_l, w_l, B, K, c->H, c->I, E, c->dtype,
+                                        c->tables + size_t(layer) * E, sptr, c->n_shared, c->ffn_ws, ebase, c->rstride,
+                                        c->s))
+                return rc;
+        } else if (int rc = moe_route_topk(x, c->router[layer], B, c->H, E, K, c->dtype, c->renorm, idx_l, w_l,
+                                           nullptr, c->route_ws, c->route_ws_bytes, c->s)) {
             return rc;
-        if (!defer_side) {
+        }
+        if (use && c->side && !defer_side) {
             STMOE_HIP(hipEventRecord(c->ev_sel, c->s));
             STMOE_HIP(hipStreamWaitEvent(c->side, c->ev_sel, 0));
             const int32_t* prev = layer > 0 ? c->idx + pbase + size_t(layer - 1) * B * K : nullptr;
@@ -539,10 +555,9 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         tl.mid = int(c->ev_used - 1);
     }
     if (int rc = ffn_launch(x, idx_l, w_l, B, K, c->H, c->I, E, c->dtype, c->tables + size_t(layer) * E,
-                            c->n_shared ? c->shared + size_t(layer) * c->n_shared : nullptr, c->n_shared,
+                            sptr, c->n_shared,
                             y, c->ffn_ws, c->s, timed ? c->n_experts : nullptr, e1,
-                            route_in_ffn ? zbuf : nullptr, c->renorm,
-                            c->rbase.empty() ? nullptr : c->rbase[size_t(layer)], c->rstride))
+                            route_in_ffn ? zbuf : nullptr, c->renorm, ebase, c->rstride, plan))
         return rc;
     if (timed) {
         if (int rc = stamp_event(tl.down1, c->s)) return rc;

@@ -19,19 +19,28 @@
 //            the L2 of every XCD), and the summation order depends only on the
 //            routing, never on where the blobs live.
 //
-// Batch < 8: GEMV kernels.  A group of G lanes (64, 32 or 16, by row length)
-// owns R rows and strides over their 16-byte chunks; the activations come
-// from L1/L2; DPP / shuffle segment sums reduce.  For long down rows the
-// whole workgroup strides one row block (split-K over its four waves).
-// Batch >= 8: MFMA kernels (v_mfma_f32_16x16x32_bf16).  The tokens form the
+// Batch 1, and bf16 shapes whose activations are held in fp32: GEMV kernels.
+// A group of G lanes (64, 32 or 16, by row length) owns R rows and strides
+// over their 16-byte chunks; the activations come from L1/L2; DPP / shuffle
+// segment sums reduce.  For long down rows the whole workgroup strides one
+// row block (split-K over its four waves).
+// Batch 2 to 8, and fp32 weights or ragged sizes beyond: 4-row tiles on the
+// 16-block 4x4 MFMA (ffn_tile.h): a step costs a slot's own tokens.
+// Batch > 8: 16-row tiles (v_mfma_f32_16x16x32_bf16).  The tokens form the
 // 16-row A operand (padded with zeros), 16 weight rows the B operand.  In
 // each 64-element step lane (n, q) loads elements 8q..8q+7 and 32+8q..32+8q+7
 // of row n, so every load instruction reads 16 full 64-byte row segments.
-// The SwiGLU activation goes through bf16.
+// With few tokens per slot the gate/up phase takes 4-row tiles.
+// On both tile paths the SwiGLU activation of bf16 weights goes through bf16.
 //
-// Every kernel rebuilds the slot plan (distinct selected experts ascending,
-// token masks) from topk_idx/topk_w in LDS: no host round trip, no planning
-// launch.
+// The slot plan (distinct selected experts ascending, token masks) is built
+// on the device.  The router's tail launch of the decode path makes it where
+// it runs (ffn_route_plan): a gate/up workgroup then reads one record, where
+// building the plan in LDS costs each round of workgroups about 2 us
+// (Qwen3-30B shapes at batch 8: 3072 workgroups in four rounds).  Otherwise
+// every gate/up workgroup rebuilds it from topk_idx/topk_w, with no host
+// round trip or planning launch, and one leaves it to the down launch; the
+// GEMV kernels rebuild it in both.
 #include <mutex>
 #include <type_traits>
 
@@ -41,7 +50,7 @@
 // Workspace of moe_expert_ffn_noalloc: one copy per GPU, held until the
 // process ends.  In host code this name is a stand-in, not a device address;
 // the device address comes from hipGetSymbolAddress (see noalloc_scratch).
-static __device__ __align__(256) unsigned char scratch[size_t(16) << 20];
+static __device__ __align__(256) unsigned char scratch[(size_t(16) << 20) + (size_t(32) << 10)];
 
 namespace stmoe {
 namespace {
@@ -51,10 +60,9 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kMaxShared = 8;
 constexpr int kMaxSlots = kMaxE + kMaxShared;
 constexpr int kDownWgTarget = 256;    // workgroups the MFMA down phase aims for
-constexpr int kMfmaMinB = 8;          // batch from which the MFMA kernels run
+constexpr int kMfmaMinB = 9;          // batch from which the 16-row MFMA kernels run
 constexpr int kUpInFlight = 2;        // 16-byte chunks per row in flight per lane (GEMV gate/up)
 constexpr bool kUpB1 = true;           // batch 1: the gate/up kernel that finds its slot in registers
-constexpr int kUpB1RouteMaxE = 128;    // ... and routes up to this many experts (in registers up to 64)
 constexpr int kShortRowChunks = 4;    // down rows with at most this many chunks per lane are short: ...
 constexpr int kDownInFlightShort = 4; // ... the lane-group down kernel loads a slot's chunks in one step
 constexpr bool kStageX = true;        // GEMV gate/up: token activations staged in LDS ...
@@ -66,6 +74,8 @@ constexpr int kDownCarryMaxNB = 4;    // lane-group down, one row per group: act
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct SlotList;
 
 struct FfnArgs {
     const void* x;                   // [B][H]
@@ -80,6 +90,10 @@ struct FfnArgs {
     float* part;                     // [ng][B][H] partial sums of the MFMA down phase (ng > 1)
     float* y;                        // [B][H]
     unsigned long long* n_experts;   // optional: += distinct routed experts (block 0)
+    SlotList* slots;          // the slot plan in global memory (null: nobody reads it)
+    int ready;                       // ... built before the gate/up launch
+    int cap;                         // slots at most
+    int act16;                       // GEMV and tile activations held in bf16
     int ng, spg;                     // expert-slot groups of the down phase, slots per group
     // optional routing prologue of the gate/up kernels: softmax + top-K of
     // these router logits [B][E] (B*E <= kRouteInFfnMax); block 0 writes the
@@ -105,30 +119,17 @@ struct PlanB : Plan {
     const char* blob[kMaxSlots];
 };
 
-// Gating (Section 2) inside a gate/up workgroup: the same steps and
-// arithmetic as the router tail, on rows of E rounded up to 4, into the
-// plan's idx/w; block 0 also publishes them.
+// Gating (Section 2) inside a gate/up workgroup: the router tail's row, one
+// wave per row, into the plan's idx/w; block 0 also publishes them.
 __device__ void route_into_plan(const FfnArgs& a, Plan& p) {
-    constexpr int kRouteRows = kRouteInFfnMax + 3 * kMaxB;
-    __shared__ __align__(16) uint32_t keys[kRouteRows];
-    __shared__ float zl[kRouteRows];
-    __shared__ int32_t win[kMaxB * kMaxK];
-    __shared__ float rowmax[kMaxB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = (a.E + 3) & ~3;
-    gating::stage_keys(a.logits, a.B, a.E, row, keys, zl);
-    gating::rank_winners(keys, zl, a.B, a.E, a.K, row, win, rowmax);
     for (int b = wave; b < a.B; b += kWaves) {
         int e;
         float wt;
-        gating::row_weights(zl, win, rowmax, b, a.E, a.K, row, a.renorm, e, wt);
-        if (lane < a.K) {
-            p.idx[b * a.K + lane] = e;
-            p.w[b * a.K + lane] = wt;
-            if (blockIdx.x == 0) {
-                const_cast<int32_t*>(a.idx)[b * a.K + lane] = e;
-                const_cast<float*>(a.w)[b * a.K + lane] = wt;
-            }
+        gating::route_row(a.logits + size_t(b) * a.E, a.E, a.K, a.renorm, p.idx + b * a.K, p.w + b * a.K, e, wt);
+        if (blockIdx.x == 0 && lane < a.K) {
+            const_cast<int32_t*>(a.idx)[b * a.K + lane] = e;
+            const_cast<float*>(a.w)[b * a.K + lane] = wt;
         }
     }
 }
@@ -427,93 +428,6 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up(FfnArgs a, int blocks_pe
     }
 }
 
-// gate/up, whole workgroup per block of R rows: the 256 lanes stride the
-// rows' chunks together (every lane issues all its loads of an iteration at
-// once), then the four waves' sums combine through LDS.
-template <bool BF, int R, int NB>
-__global__ __launch_bounds__(kThreads) void ffn_gate_up_wg(FfnArgs a, int blocks_per_slot, int act16) {
-    __shared__ Plan p;
-    __shared__ float red[kWaves][2][R][NB];
-    build_plan(a, p, true);
-    const int j = blockIdx.x / blocks_per_slot;
-    if (j >= p.n_slots) return;
-    const int i0 = (blockIdx.x % blocks_per_slot) * R;
-    if (i0 >= a.I) return;   // I is a multiple of R
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const unsigned tm = p.tok[j];
-    constexpr int esz = BF ? 2 : 4;
-    const size_t rowb = size_t(a.H) * esz;
-    const char* blob = slot_blob(a, p, j);
-    const char* wg = blob + size_t(i0) * rowb;
-    const char* wu = blob + size_t(a.I) * rowb + size_t(i0) * rowb;
-    const char* xs = reinterpret_cast<const char*>(a.x);
-    const int cpr = int(rowb / 16);
-
-    float accg[R][NB], accu[R][NB];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) accg[r][b] = accu[r][b] = 0.f;
-
-    auto compute = [&](int c, const uint4 (&qg)[R], const uint4 (&qu)[R]) {
-        Chunk<BF> cg[R], cu[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) { cg[r].unpack(qg[r]); cu[r].unpack(qu[r]); }
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            if (!((tm >> b) & 1u)) continue;
-            Chunk<BF> cx;
-            cx.unpack(ld_cached(xs + b * rowb + size_t(c) * 16));
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                accg[r][b] = dotc<BF>(cg[r], cx, accg[r][b]);
-                accu[r][b] = dotc<BF>(cu[r], cx, accu[r][b]);
-            }
-        }
-    };
-    int c = tid;
-    for (; c + kThreads < cpr; c += 2 * kThreads) {
-        uint4 ga[R], ua[R], gb[R], ub[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ga[r] = ld_stream(wg + r * rowb + size_t(c) * 16);
-            ua[r] = ld_stream(wu + r * rowb + size_t(c) * 16);
-            gb[r] = ld_stream(wg + r * rowb + size_t(c + kThreads) * 16);
-            ub[r] = ld_stream(wu + r * rowb + size_t(c + kThreads) * 16);
-        }
-        compute(c, ga, ua);
-        compute(c + kThreads, gb, ub);
-    }
-    if (c < cpr) {
-        uint4 ga[R], ua[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ga[r] = ld_stream(wg + r * rowb + size_t(c) * 16);
-            ua[r] = ld_stream(wu + r * rowb + size_t(c) * 16);
-        }
-        compute(c, ga, ua);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            if (!((tm >> b) & 1u)) continue;
-            const float gs = wave_sum(accg[r][b]);
-            const float us = wave_sum(accu[r][b]);
-            if (lane == 0) { red[wave][0][r][b] = gs; red[wave][1][r][b] = us; }
-        }
-    __syncthreads();
-    if (tid < R * NB) {
-        const int r = tid / NB, b = tid % NB;
-        if ((tm >> b) & 1u) {
-            float gs = 0.f, us = 0.f;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) { gs += red[w][0][r][b]; us += red[w][1][r][b]; }
-            store_act(a.act, act16, (size_t(j) * a.B + b) * a.I + i0 + r, slot_weight(a, p, j, b) * silu(gs) * us);
-        }
-    }
-}
-
 // ---------------------------------------------------------------- batch 1
 // One token: every routed slot serves it, so the slot plan reduces to the
 // selection ordered by expert index.  The batch-1 gate/up kernel finds its
@@ -527,12 +441,6 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_wg(FfnArgs a, int blocks
 __device__ __forceinline__ int lane_i(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 __device__ __forceinline__ float lane_f(float v, int src) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
-}
-
-// n-th set bit (n >= 0) of a uniform 64-bit mask, or -1.
-__device__ __forceinline__ int nth_bit(unsigned long long m, int n) {
-    for (int q = 0; q < n && m; ++q) m &= m - 1ull;
-    return m ? __ffsll(m) - 1 : -1;
 }
 
 // Selection given: lane k < K holds idx[k].  Slots are the row's distinct
@@ -562,79 +470,18 @@ __device__ __forceinline__ int b1_given(const FfnArgs& a, int j, float& wj, int&
     return lane_i(v, src);
 }
 
-// Router logits given (used up to 64 experts, correct up to 128): the router
-// tail's softmax / top-K in registers, lanes f and f + 64 holding expert f
-// and f + 64.  The same order
-// keys and the same count of the keys that beat each expert (larger key, or
-// equal key at a lower index) give the same winners; the softmax sum takes
-// each lane's terms in the tail's order into the same wave sum, and lane k
-// holds the probability of the position-k winner as in the tail, so the
-// weights are bit-identical too.  Block 0 publishes idx/w.
-__device__ __forceinline__ int b1_routed(const FfnArgs& a, int j, float& wj, int& n_routed) {
-    const int E = a.E, K = a.K, lane = threadIdx.x & 63;
-    const float z0 = lane < E ? a.logits[lane] : 0.f;
-    const float z1 = lane + 64 < E ? a.logits[lane + 64] : 0.f;
-    const uint32_t k0 = lane < E ? gating::order_key(z0) : 0u;
-    const uint32_t k1 = lane + 64 < E ? gating::order_key(z1) : 0u;
-    int c0 = 0, c1 = 0;
-    const int e0 = E < 64 ? E : 64;
-#pragma unroll 8
-    for (int g = 0; g < e0; ++g) {
-        const uint32_t kg = uint32_t(lane_i(int(k0), g));
-        c0 += kg > k0 || (kg == k0 && g < lane);
-        c1 += kg > k1;
-    }
-#pragma unroll 8
-    for (int g = 64; g < E; ++g) {
-        const uint32_t kg = uint32_t(lane_i(int(k1), g - 64));
-        c0 += kg > k0;
-        c1 += kg > k1 || (kg == k1 && g < lane + 64);
-    }
-    const bool w0 = lane < E && c0 < K, w1 = lane + 64 < E && c1 < K;
-    const unsigned long long W0 = __ballot(w0), W1 = __ballot(w1);
-    // the row max is the logit of the position-0 winner
-    const unsigned long long t0 = __ballot(w0 && c0 == 0), t1 = __ballot(w1 && c1 == 0);
-    const float m = t0 ? lane_f(z0, __ffsll(t0) - 1) : lane_f(z1, __ffsll(t1) - 1);
-    float s = 0.f;
-    if (lane < E) s += expf(z0 - m);
-    if (lane + 64 < E) s += expf(z1 - m);
-    s = wave_sum(s);
-    // lane k < K: expert and probability of the position-k winner
-    int ek = 0;
-    for (int k = 0; k < K; ++k) {
-        const unsigned long long q0 = __ballot(w0 && c0 == k), q1 = __ballot(w1 && c1 == k);
-        const int f = q0 ? __ffsll(q0) - 1 : 64 + __ffsll(q1) - 1;
-        if (lane == k) ek = f;
-    }
-    const float zk0 = __shfl(z0, ek & 63, 64), zk1 = __shfl(z1, ek & 63, 64);
-    float p = 0.f;
-    if (lane < K) p = expf((ek < 64 ? zk0 : zk1) - m) / s;
-    const float wsum = wave_sum(p);
-    const float wt = a.renorm ? p / wsum : p;
+// Router logits given: every wave routes the token in registers (the router
+// tail's row, so selection and weights are bit-identical); slot j is the j-th
+// smallest of the K winners.  Block 0 publishes idx/w.
+__device__ __forceinline__ int b1_routed(const FfnArgs& a, int j, float& wj, int& n_routed, int32_t* sel, float* prob) {
+    const int K = a.K, lane = threadIdx.x & 63;
+    int ek;
+    float wk;
+    gating::route_row(a.logits, a.E, K, a.renorm, sel, prob, ek, wk);
     if (blockIdx.x == 0 && threadIdx.x < K) {
         const_cast<int32_t*>(a.idx)[lane] = ek;
-        const_cast<float*>(a.w)[lane] = wt;
+        const_cast<float*>(a.w)[lane] = wk;
     }
-    n_routed = __popcll(W0) + __popcll(W1);
-    if (j >= n_routed) return -1;
-    const int n0 = __popcll(W0);
-    const int e = j < n0 ? nth_bit(W0, j) : 64 + nth_bit(W1, j - n0);
-    const int pos = e < 64 ? lane_i(c0, e) : lane_i(c1, e - 64);
-    wj = lane_f(wt, pos);
-    return e;
-}
-
-// Router logits given, 64 < E <= 128: too many experts for every wave to
-// rank on its own, so the workgroup runs the lane-group kernel's gating
-// (route_into_plan: the router tail's steps, bit-identical) and only skips
-// the slot plan after it: slot j is the j-th smallest of the K winners,
-// found in registers.
-__device__ __forceinline__ int b1_routed_lds(const FfnArgs& a, int j, float& wj, int& n_routed, Plan& p) {
-    const int K = a.K, lane = threadIdx.x & 63;
-    route_into_plan(a, p);
-    __syncthreads();
-    const int ek = lane < K ? p.idx[lane] : 0;
-    const float wk = lane < K ? p.w[lane] : 0.f;
     n_routed = K;
     if (j >= K) return -1;
     int place = 0;
@@ -651,12 +498,11 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
     constexpr int U = kUpInFlight;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = blockIdx.x / blocks_per_slot;
-    __shared__ Plan p;
+    __shared__ int32_t sel[kWaves][kMaxK];
+    __shared__ float prob[kWaves][kMaxK];
     float wj = 1.f;
     int n_routed = 0;
-    const int e = !a.logits      ? b1_given(a, j, wj, n_routed)
-                  : a.E <= 64    ? b1_routed(a, j, wj, n_routed)
-                                 : b1_routed_lds(a, j, wj, n_routed, p);
+    const int e = a.logits ? b1_routed(a, j, wj, n_routed, sel[wave], prob[wave]) : b1_given(a, j, wj, n_routed);
     const char* blob;
     if (e >= 0) {
         blob = routed_blob(a, e);
@@ -727,6 +573,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
         if (g == 0) store_act(a.act, act16, size_t(j) * a.I + i0 + r, wj * silu(gs) * us);
     }
 }
+
+#include "ffn_tile.h"
 
 // One slot's contribution to R down rows: chunk steps c0, c0 + S, ... of
 // the rows, U steps in flight.  With CARRY the activation chunks of the
@@ -1007,22 +855,43 @@ __global__ __launch_bounds__(kThreads) void ffn_down_wg(FfnArgs a) {
 // MFMA path (batch >= 8, bf16, H and I multiples of 64)
 // ============================================================================
 
+// Slot j of a gate/up workgroup: from the plan made beforehand, or built here
+// (workgroup 0 then publishes it for the down launch).  False: no such slot.
+__device__ bool mfma_slot(const FfnArgs& a, Plan& p, int j, const char*& blob, unsigned& tm) {
+    if (a.ready) {
+        const SlotRec& r = a.slots->rec[j];
+        blob = r.blob;
+        tm = r.tok;
+        return r.nt != 0;
+    }
+    build_plan(a, p, true);
+    if (blockIdx.x == 0) publish_plan<kThreads>(a, p.idx, p.w);
+    if (j >= p.n_slots) return false;
+    blob = slot_blob(a, p, j);
+    tm = p.tok[j];
+    return true;
+}
+
+// Gate weight of token b, which the slot serves.
+__device__ __forceinline__ float mfma_weight(const FfnArgs& a, const Plan& p, int j, unsigned tm, int b) {
+    return a.ready ? a.slots->rec[j].w[__popc(tm & ((1u << b) - 1u))] : slot_weight(a, p, j, b);
+}
+
 // gate/up: each wave computes NT tiles of 16 rows x 16 tokens for W_gate and
 // W_up over the whole hidden dimension, then writes the bf16 activation
 // (zero for tokens not routed to the slot).
 template <int NT>
 __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma(FfnArgs a, int blocks_per_slot) {
     __shared__ Plan p;
-    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    if (j >= p.n_slots) return;
+    const char* blob;
+    unsigned tm;
+    if (!mfma_slot(a, p, j, blob, tm)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = (blockIdx.x % blocks_per_slot) * (kWaves * NT * 16) + wave * NT * 16;
     if (i0 >= a.I) return;   // I is a multiple of 16
-    const unsigned tm = p.tok[j];
     const size_t rowb = size_t(a.H) * 2;
-    const char* blob = slot_blob(a, p, j);
     const bool xrow = n < a.B;     // A operand row n = token n
     const char* xs = reinterpret_cast<const char*>(a.x) + size_t(xrow ? n : 0) * rowb + q * 16;
     const char* wg[NT];
@@ -1089,7 +958,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma(FfnArgs a, int bloc
         const int b = 4 * q + r;
         if (b >= a.B) continue;
         const bool routed = (tm >> b) & 1u;
-        const float wb = routed ? slot_weight(a, p, j, b) : 0.f;
+        const float wb = routed ? mfma_weight(a, p, j, tm, b) : 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = routed ? wb * silu(dg[t][r]) * du[t][r] : 0.f;
@@ -1118,9 +987,10 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
     __shared__ Plan p;
     __shared__ float red[SK ? kWaves : 1][2][64][4];
     extern __shared__ uint4 stage[];
-    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    if (j >= p.n_slots) return;
+    const char* blob;
+    unsigned tm;
+    if (!mfma_slot(a, p, j, blob, tm)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = SK ? (blockIdx.x % blocks_per_slot) * 16
@@ -1130,9 +1000,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
     constexpr int kLoads = kRows / 4;        // load instructions per step (four rows each)
     const int h_lo = SK ? wave * (a.H / kWaves) : 0;           // SK: H is a multiple of 512
     const int h_hi = SK ? h_lo + a.H / kWaves : a.H;
-    const unsigned tm = p.tok[j];
     const size_t rowb = size_t(a.H) * 2;
-    const char* blob = slot_blob(a, p, j);
     uint4* my = stage + size_t(wave) * kRows * kLdsPadU4;
     // loader mapping: lane (g, e) loads uint4 e of the segment of row 4r + g
     const int g = lane >> 4, e = lane & 15;
@@ -1215,7 +1083,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
         const int b = 4 * q + r;
         if (b >= a.B) continue;
         const bool routed = (tm >> b) & 1u;
-        const float wb = routed ? slot_weight(a, p, j, b) : 0.f;
+        const float wb = routed ? mfma_weight(a, p, j, tm, b) : 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = routed ? wb * silu(dg[t][r]) * du[t][r] : 0.f;
@@ -1229,9 +1097,9 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
 // the slots of the workgroup's group.
 template <int NT>
 __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
-    __shared__ PlanB p;
+    __shared__ SlotTable p;
     extern __shared__ uint4 stage[];
-    build_plan(a, p);
+    load_slots(a, p);
     const int rb = blockIdx.x / a.ng, grp = blockIdx.x % a.ng;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
@@ -1260,8 +1128,11 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
     const int total = live ? (j1 - j0) * steps : 0;
     uint4 ld[kLoads];
     bf16x8 av[4], an[4];
-    auto issue = [&](int j, int k, bf16x8 (&ax)[4]) {
-        const char* wd = slot_blob(a, p, j) + 2 * size_t(a.I) * a.H * 2 + size_t(k) * 2;
+    // only routed tokens' activations exist: the other rows are zero operands
+    bool rt = false, rn = false;
+    auto issue = [&](int j, int k, bf16x8 (&ax)[4], bool& routed) {
+        routed = (p.tok[j] >> n) & 1u;
+        const char* wd = p.blob[j] + 2 * size_t(a.I) * a.H * 2 + size_t(k) * 2;
         const char* ar = reinterpret_cast<const char*>(a.act) + (size_t(j) * a.B + (arow ? n : 0)) * rowb +
                          q * 16 + size_t(k) * 2;
 #pragma unroll
@@ -1271,7 +1142,7 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
     };
     int jn = j0, kn = 0;                            // next step to issue
     if (total > 0) {
-        issue(jn, kn, av);
+        issue(jn, kn, av, rt);
         if ((kn += 128) == a.I) { kn = 0; ++jn; }
     }
     for (int s = 0; s < total; ++s) {
@@ -1284,12 +1155,12 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const bool more = s + 1 < total;
         if (more) {
-            issue(jn, kn, an);
+            issue(jn, kn, an, rn);
             if ((kn += 128) == a.I) { kn = 0; ++jn; }
         }
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
-            const bf16x8 ax = arow ? av[kb] : zero;
+            const bf16x8 ax = rt ? av[kb] : zero;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const bf16x8 wv = __builtin_bit_cast(bf16x8, my[(t * 16 + n) * kLdsPadU4 + kb * 4 + q]);
@@ -1299,6 +1170,7 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
         if (more) {
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) av[kb] = an[kb];
+            rt = rn;
         }
     }
     float* out = a.ng == 1 ? a.y : a.part + size_t(grp) * a.B * a.H;
@@ -1317,15 +1189,14 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
 __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_sk(FfnArgs a, int blocks_per_slot) {
     __shared__ Plan p;
     __shared__ float red[kWaves][2][64][4];
-    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    if (j >= p.n_slots) return;
+    const char* blob;
+    unsigned tm;
+    if (!mfma_slot(a, p, j, blob, tm)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = (blockIdx.x % blocks_per_slot) * 16;   // I is a multiple of 16
-    const unsigned tm = p.tok[j];
     const size_t rowb = size_t(a.H) * 2;
-    const char* blob = slot_blob(a, p, j);
     const bool xrow = n < a.B;
     const int hq = a.H / kWaves;                            // H is a multiple of 256
     const size_t kbase = size_t(wave) * hq * 2 + q * 16;
@@ -1375,7 +1246,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_sk(FfnArgs a, int b
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) { g += red[w][0][lane][r]; u += red[w][1][lane][r]; }
         const bool routed = (tm >> b) & 1u;
-        const float v = routed ? slot_weight(a, p, j, b) * silu(g) * u : 0.f;
+        const float v = routed ? mfma_weight(a, p, j, tm, b) * silu(g) * u : 0.f;
         act[size_t(b) * a.I + i0 + n] = f32_to_bf16_rne(v);
     }
 }
@@ -1384,8 +1255,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_sk(FfnArgs a, int b
 // the slots of its group (A operand = the slot's bf16 activations).
 template <int NT>
 __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
-    __shared__ Plan p;
-    build_plan(a, p);
+    __shared__ SlotTable p;
+    load_slots(a, p);
     const int rb = blockIdx.x / a.ng, grp = blockIdx.x % a.ng;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
@@ -1403,10 +1274,11 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
     for (int t = 0; t < NT; ++t) d[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bf16x8 zero = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
     for (int j = j0; live && j < j1; ++j) {
-        const char* wd = slot_blob(a, p, j) + 2 * size_t(a.I) * a.H * 2 + q * 16;
+        const char* wd = p.blob[j] + 2 * size_t(a.I) * a.H * 2 + q * 16;
         const char* wr[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) wr[t] = wd + size_t(h0 + t * 16 + n) * rowb;
+        const bool rt = (p.tok[j] >> n) & 1u;      // only routed tokens' activations exist
         const char* ar = reinterpret_cast<const char*>(a.act) +
                          (size_t(j) * a.B + (arow ? n : 0)) * rowb + q * 16;
         auto step = [&](const bf16x8 (&w0)[NT], const bf16x8 (&w1)[NT], const bf16x8& a0, const bf16x8& a1) {
@@ -1427,8 +1299,8 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
                 wa1[t] = ld_bf8_stream(wr[t] + o1);
                 wb1[t] = ld_bf8_stream(wr[t] + o1 + 64);
             }
-            const bf16x8 aa0 = arow ? ld_bf8(ar + o0) : zero, ab0 = arow ? ld_bf8(ar + o0 + 64) : zero;
-            const bf16x8 aa1 = arow ? ld_bf8(ar + o1) : zero, ab1 = arow ? ld_bf8(ar + o1 + 64) : zero;
+            const bf16x8 aa0 = rt ? ld_bf8(ar + o0) : zero, ab0 = rt ? ld_bf8(ar + o0 + 64) : zero;
+            const bf16x8 aa1 = rt ? ld_bf8(ar + o1) : zero, ab1 = rt ? ld_bf8(ar + o1 + 64) : zero;
             step(wa0, wb0, aa0, ab0);
             step(wa1, wb1, aa1, ab1);
         }
@@ -1440,7 +1312,7 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
                 wa0[t] = ld_bf8_stream(wr[t] + o0);
                 wb0[t] = ld_bf8_stream(wr[t] + o0 + 64);
             }
-            const bf16x8 aa0 = arow ? ld_bf8(ar + o0) : zero, ab0 = arow ? ld_bf8(ar + o0 + 64) : zero;
+            const bf16x8 aa0 = rt ? ld_bf8(ar + o0) : zero, ab0 = rt ? ld_bf8(ar + o0 + 64) : zero;
             step(wa0, wb0, aa0, ab0);
         }
     }
@@ -1489,10 +1361,13 @@ int pick_group(int chunks) {
 }
 
 struct Shape {
-    bool mfma;          // MFMA path
+    bool mfma;          // 16-row MFMA path (batch > 8)
+    bool tile;          // 4-row tile path
+    bool tile_up;       // 16-row MFMA path: gate/up on 4-row tiles
     int slots;          // slot capacity
     int gu_G;           // GEMV gate/up lanes per row
-    int dn_kind;        // 0: rows (lane groups, slots split over waves), 1: whole-workgroup rows, 2: MFMA
+    int dn_kind;        // 0: rows (lane groups, slots split over waves), 1: whole-workgroup rows, 2: MFMA,
+                        // 3: 4-row tiles
     int dn_G;           // lanes per row for kind 0
     int dn_rows;        // rows per down workgroup
     int n_rb;           // down row blocks
@@ -1503,21 +1378,33 @@ struct Shape {
 
 constexpr int kDownRowsWgTarget = 1024;  // lane-group down: fewest workgroups more rows per group may leave
 constexpr int kDownWgR = 4;   // rows per workgroup (whole-workgroup down)
-constexpr int kUpWgR = 0;     // rows per workgroup of the whole-workgroup gate/up kernel (0: lane groups)
 constexpr int kDownForceG = 0;  // lanes per down row (0: by row length)
 constexpr int kMfmaNT = 0;      // 1: force one 16-row tile per wave in the MFMA gate/up kernel
-constexpr int kMfmaDownNT = 2;  // 16-row tiles per wave of the MFMA down kernel (1, 2 or 4)
+constexpr int kMfmaDownNT = 2;  // 16-row tiles per wave of the MFMA down kernel (1 or 2)
 constexpr int kMfmaSplitKBelow = 2048;  // split-K MFMA gate/up when the tiled grid has fewer workgroups
 constexpr bool kMfmaUpLds = true;       // MFMA gate/up stages weight rows through LDS (H % 128 == 0;
                                         // split-K: H % 512 == 0)
 constexpr bool kMfmaDownLds = true;     // MFMA down stages W_down rows through LDS (I % 128 == 0)
-constexpr int kUpWgMinChunks = 512;   // ... used when a row has at least this many chunks
+
+// GEMV activations are bf16 for the lane-group down kernel below four rows
+// per group and the whole-workgroup one up to two token columns, fp32
+// otherwise (there the unpacking registers cost more than the traffic
+// saves); the gate/up launch writes what its down kernel reads.
+template <bool BF>
+int act_bf16(const Shape& s, int B) { return BF && (s.dn_kind == 1 ? B <= 2 : s.dn_R < 4); }
 
 Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     Shape s{};
     const int esz = dtype == STMOE_BF16 ? 2 : 4;
     s.slots = (B * K < E ? B * K : E) + n_shared;
     s.mfma = dtype == STMOE_BF16 && B >= kMfmaMinB && H % 64 == 0 && I % 64 == 0;
+    // A 4-row tile costs one operand load and one product per four tokens of
+    // a slot, a 16-row one the same for 1 to 16: few tokens per slot take the
+    // former (Qwen3-235B shapes at batch 16, 1.6 per slot: gate/up 332 -> 313
+    // us), shared experts (all tokens) and few experts the latter
+    // (DeepSeek-V2-Lite shapes at batch 12: FFN 130 us against 136;
+    // Mixtral shapes at batch 16: 445 against 496).
+    s.tile_up = s.mfma && n_shared == 0 && B * K <= 2 * E;
     s.gu_G = pick_group(H * esz / 16);
     const int cpr_i = I * esz / 16;
     s.ng = s.spg = 1;
@@ -1544,6 +1431,17 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
             s.dn_R *= 2;
         s.dn_rows = (64 / s.dn_G) * s.dn_R;
     }
+    // Which activations are held in bf16 is the same on every path: at batch 8
+    // where the sizes are multiples of 64, else where the GEMV down kernel
+    // takes them so.  bf16 shapes with fp32 activations keep the GEMV kernels
+    // (three bf16 operands per activation on the matrix cores summed to 5.0e-7
+    // of the 64-bit result, the GEMV to 3.1e-7).
+    const bool act16 = dtype == STMOE_BF16 && ((B == 8 && H % 64 == 0 && I % 64 == 0) || act_bf16<true>(s, B));
+    s.tile = B >= 2 && !s.mfma && (dtype == STMOE_F32 || act16);
+    if (s.tile) {
+        s.dn_kind = 3;
+        return s;
+    }
     s.n_rb = (H + s.dn_rows - 1) / s.dn_rows;
     if (s.mfma) {
         int ng = (kDownWgTarget + s.n_rb - 1) / s.n_rb;
@@ -1555,8 +1453,11 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     return s;
 }
 
+constexpr size_t kSlotListBytes = (sizeof(SlotList) + 255) / 256 * 256;
+static_assert(kSlotListBytes <= sizeof(scratch) - (size_t(16) << 20), "scratch too small");
+
 struct WsLayout {
-    size_t act, part, total;
+    size_t act, part, slots, total;
 };
 
 WsLayout ws_layout(int B, int H, int I, const Shape& s) {
@@ -1564,16 +1465,10 @@ WsLayout ws_layout(int B, int H, int I, const Shape& s) {
     WsLayout w{};
     w.act = 0;
     w.part = up(size_t(s.slots) * B * I * sizeof(float));
-    w.total = w.part + (s.ng > 1 ? up(size_t(s.ng) * B * H * sizeof(float)) : 0);
+    w.slots = w.part + (s.ng > 1 ? up(size_t(s.ng) * B * H * sizeof(float)) : 0);
+    w.total = w.slots + kSlotListBytes;
     return w;
 }
-
-// GEMV activations are bf16 for the lane-group down kernel below four rows
-// per group and the whole-workgroup one up to two token columns, fp32
-// otherwise (there the unpacking registers cost more than the traffic
-// saves); the gate/up launch writes what its down kernel reads.
-template <bool BF>
-int act_bf16(const Shape& s, int B) { return BF && (s.dn_kind == 1 ? B <= 2 : s.dn_R < 4); }
 
 template <bool BF, int G, int NB, int R>
 int launch_gate_up_r(const FfnArgs& a, const Shape& s, hipStream_t st) {
@@ -1582,7 +1477,7 @@ int launch_gate_up_r(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const size_t xbytes = size_t(a.B) * a.H * (BF ? 2 : 4);
     const int act16 = act_bf16<BF>(s, a.B);
     if constexpr (kUpB1 && NB == 1) {
-        if (a.B == 1 && (!a.logits || a.E <= kUpB1RouteMaxE)) {
+        if (a.B == 1) {
             hipLaunchKernelGGL((ffn_gate_up_b1<BF, G, R>), dim3(unsigned(bps * s.slots)), dim3(kThreads), 0, st, a,
                                bps, act16);
             STMOE_LAUNCHED();
@@ -1601,15 +1496,6 @@ int launch_gate_up_r(const FfnArgs& a, const Shape& s, hipStream_t st) {
 
 template <bool BF, int G, int NB>
 int launch_gate_up(const FfnArgs& a, const Shape& s, hipStream_t st) {
-    if constexpr (kUpWgR > 0) {
-        if (a.H * (BF ? 2 : 4) / 16 >= kUpWgMinChunks && a.I % kUpWgR == 0) {
-            const int bps = a.I / kUpWgR;
-            hipLaunchKernelGGL((ffn_gate_up_wg<BF, kUpWgR, NB>), dim3(unsigned(bps * s.slots)),
-                               dim3(kThreads), 0, st, a, bps, act_bf16<BF>(s, a.B));
-            STMOE_LAUNCHED();
-            return STMOE_OK;
-        }
-    }
     // every workgroup stages all token activations; from 4 token columns on
     // two rows per lane group halve that traffic, below it one row per group
     // gives more workgroups in flight (I is a multiple of 8)
@@ -1620,6 +1506,10 @@ int launch_gate_up(const FfnArgs& a, const Shape& s, hipStream_t st) {
 template <bool BF, int NB, int U>
 void launch_down_rows_u(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const dim3 grid(unsigned(s.n_rb));
+    if constexpr (NB > 1) {      // four rows per group, or the shape takes 4-row tiles
+        hipLaunchKernelGGL((ffn_down_rows<BF, 64, 4, NB, U>), grid, dim3(kThreads), 0, st, a);
+        return;
+    }
     if (s.dn_G == 16)
         hipLaunchKernelGGL((ffn_down_rows<BF, 16, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
     else if (s.dn_G == 32 && s.dn_R == 2)
@@ -1668,18 +1558,74 @@ int launch_gemv(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_
 
 template <bool BF>
 int launch_gemv_b(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
-    if (a.B <= 1) return launch_gemv<BF, 1>(a, s, st, ev_mid);
-    if (a.B <= 2) return launch_gemv<BF, 2>(a, s, st, ev_mid);
-    if (a.B <= 4) return launch_gemv<BF, 4>(a, s, st, ev_mid);
-    if (a.B <= 8) return launch_gemv<BF, 8>(a, s, st, ev_mid);
-    return launch_gemv<BF, 16>(a, s, st, ev_mid);
+    if constexpr (BF) {      // fp32 weights run on tiles from batch 2
+        if (a.B > 8) return launch_gemv<BF, 16>(a, s, st, ev_mid);
+        if (a.B > 4) return launch_gemv<BF, 8>(a, s, st, ev_mid);
+        if (a.B > 2) return launch_gemv<BF, 4>(a, s, st, ev_mid);
+        if (a.B > 1) return launch_gemv<BF, 2>(a, s, st, ev_mid);
+    }
+    return launch_gemv<BF, 1>(a, s, st, ev_mid);
+}
+
+// -------------------------------------------------------------- tile kernels
+
+template <bool BF, int TG>
+void launch_up_tile(const FfnArgs& a, hipStream_t st) {
+    const int extra = a.ready ? 0 : 1;       // the workgroup that publishes the plan
+    // split the columns over the waves where each wave keeps two steps of them
+    // (DeepSeek-V2-Lite shapes at batch 4: 43.2 us split, 47.6 not; rows of
+    // 1408 bytes at batch 14, gate/up + down: 49.5 against 36.2)
+    const bool sk = a.H * (BF ? 2 : 4) >= 2 * kWaves * 256;
+    const int rows = sk ? 4 : 4 * kWaves, bps = (a.I + rows - 1) / rows;
+    const dim3 grid(unsigned(bps * a.cap + extra));
+    if (sk) hipLaunchKernelGGL((ffn_up_tile<BF, TG, true>), grid, dim3(kThreads), 0, st, a, bps);
+    else hipLaunchKernelGGL((ffn_up_tile<BF, TG, false>), grid, dim3(kThreads), 0, st, a, bps);
+}
+
+template <bool BF, int RQ, int TG>
+void launch_down_tile_r(const FfnArgs& a, hipStream_t st) {
+    const dim3 grid(unsigned(a.H / (4 * RQ))), block(64 * kDownWaves);
+    if (a.I * (BF ? 2 : 4) % 256)
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, true>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, false>), grid, block, 0, st, a);
+}
+
+template <bool BF, int TG>
+void launch_down_tile(const FfnArgs& a, hipStream_t st) {
+    // Two row quads per wave share each activation load (Qwen3-30B shapes at
+    // batch 8: 29.1 us against 34.9), one gives twice the workgroups (H 1024
+    // fp32, batch 8: 15.9 against 23.1).  One workgroup of the former fills a
+    // CU: compare the rows of the busiest CU, a row at about 9/8 in the latter.
+    const int rows2 = (a.H / 8 + 255) / 256 * 8, rows1 = (a.H / 4 + 255) / 256 * 4;
+    if (8 * rows2 <= 9 * rows1) launch_down_tile_r<BF, 2, TG>(a, st);
+    else launch_down_tile_r<BF, 1, TG>(a, st);
+}
+
+template <bool BF, int TG>
+int launch_tile_t(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
+    launch_up_tile<BF, TG>(a, st);
+    STMOE_LAUNCHED();
+    if (ev_mid) STMOE_HIP(hipEventRecord(ev_mid, st));
+    launch_down_tile<BF, TG>(a, st);
+    STMOE_LAUNCHED();
+    return STMOE_OK;
+}
+
+template <bool BF>
+int launch_tile(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
+    if (a.B <= 4) return launch_tile_t<BF, 1>(a, st, ev_mid);
+    if (a.B <= 8) return launch_tile_t<BF, 2>(a, st, ev_mid);
+    return launch_tile_t<BF, 4>(a, st, ev_mid);
 }
 
 int launch_mfma(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
     // two 16-row tiles per wave when that still leaves >= 1024 workgroups
     constexpr int NT = 2;
     const int rows = kWaves * NT * 16;
-    if ((a.I / (kWaves * 16)) * s.slots < kMfmaSplitKBelow && a.H % 256 == 0) {
+    if (s.tile_up) {
+        launch_up_tile<true, 4>(a, st);
+    } else if ((a.I / (kWaves * 16)) * s.slots < kMfmaSplitKBelow && a.H % 256 == 0) {
         const int bps = a.I / 16;
         if (kMfmaUpLds && a.H % 512 == 0) {
             const unsigned lds = unsigned(kWaves * 2 * 16 * kLdsPadU4 * sizeof(uint4));
@@ -1714,10 +1660,7 @@ int launch_mfma(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_
     const dim3 dgrid(unsigned(s.n_rb * s.ng));
     const unsigned dlds = unsigned(kWaves * s.dn_nt * 16 * kLdsPadU4 * sizeof(uint4));
     const bool dn_lds = kMfmaDownLds && a.I % 128 == 0;
-    if (s.dn_nt == 4) {
-        if (dn_lds) hipLaunchKernelGGL((ffn_down_mfma_lds<4>), dgrid, dim3(kThreads), dlds, st, a);
-        else hipLaunchKernelGGL((ffn_down_mfma<4>), dgrid, dim3(kThreads), 0, st, a);
-    } else if (s.dn_nt == 2) {
+    if (s.dn_nt == 2) {
         if (dn_lds) hipLaunchKernelGGL((ffn_down_mfma_lds<2>), dgrid, dim3(kThreads), dlds, st, a);
         else hipLaunchKernelGGL((ffn_down_mfma<2>), dgrid, dim3(kThreads), 0, st, a);
     } else {
@@ -1741,21 +1684,13 @@ size_t ffn_workspace_bytes(int B, int K, int E, int H, int I, int n_shared, int 
     return ws_layout(B, H, I, s).total;
 }
 
-// Internal entry used by the decode-layer orchestration (no argument checks).
-// With `logits` (B*E <= kRouteInFfnMax) the gate/up kernel routes first and
-// idx/w are outputs, written before the down kernel reads them.
-int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
-               int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
-               float* y, void* ws, hipStream_t st, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride) {
-    if (logits && B * E > kRouteInFfnMax) {
-        set_error("ffn_launch: routing inside the FFN needs B*E <= 128");
-        return STMOE_EINVAL;
-    }
-    const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
+namespace {
+FfnArgs ffn_args(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E, int dtype,
+                 const void* const* eptr, const void* const* sptr, int n_shared, float* y, void* ws,
+                 const void* ebase, size_t estride, const Shape& s) {
     const WsLayout L = ws_layout(B, H, I, s);
     char* base = reinterpret_cast<char*>(ws);
-    FfnArgs a;
+    FfnArgs a{};
     a.x = x;
     a.idx = idx;
     a.w = w;
@@ -1772,12 +1707,64 @@ int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, 
     a.act = base + L.act;
     a.part = reinterpret_cast<float*>(base + L.part);
     a.y = y;
-    a.n_experts = n_experts;
+    a.slots = reinterpret_cast<SlotList*>(base + L.slots);
+    a.cap = s.slots;
+    a.act16 = dtype == STMOE_BF16;
     a.ng = s.ng;
     a.spg = s.spg;
+    return a;
+}
+}  // namespace
+
+// Whether the FFN of these shapes can start from a plan made beforehand
+// (ffn_route_plan).
+bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype) {
+    const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
+    return s.mfma || s.tile;
+}
+
+// The router's tail (from the logits z [B][E], writing idx/w) and the FFN's
+// slot plan, one launch.  The workspace is the FFN's.
+int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
+                   const void* const* eptr, const void* const* sptr, int n_shared, void* ws, const void* ebase,
+                   size_t estride, hipStream_t st) {
+    const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
+    const FfnArgs a = ffn_args(nullptr, idx, w, B, K, H, I, E, dtype, eptr, sptr, n_shared, nullptr, ws, ebase,
+                               estride, s);
+    gating::RouteArgs r{};
+    r.B = B;
+    r.H = H;
+    r.E = E;
+    r.K = K;
+    r.renorm = renorm ? 1 : 0;
+    r.idx = idx;
+    r.w = w;
+    r.zbuf = const_cast<float*>(z);
+    hipLaunchKernelGGL(route_plan_kernel, dim3(1), dim3(1024), 0, st, r, a);
+    STMOE_LAUNCHED();
+    return STMOE_OK;
+}
+
+// Internal entry used by the decode-layer orchestration (no argument checks).
+// With `logits` (B*E <= kRouteInFfnMax) the gate/up kernel routes first and
+// idx/w are outputs, written before the down kernel reads them.  `ready`: the
+// plan is in the workspace (ffn_route_plan on this stream).
+int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
+               int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
+               float* y, void* ws, hipStream_t st, unsigned long long* n_experts, hipEvent_t ev_mid,
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready) {
+    if (logits && B * E > kRouteInFfnMax) {
+        set_error("ffn_launch: routing inside the FFN needs B*E <= 128");
+        return STMOE_EINVAL;
+    }
+    const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
+    FfnArgs a = ffn_args(x, idx, w, B, K, H, I, E, dtype, eptr, sptr, n_shared, y, ws, ebase, estride, s);
+    a.n_experts = n_experts;
     a.logits = logits;
     a.renorm = renorm;
+    a.ready = ready;
     if (s.mfma) return launch_mfma(a, s, st, ev_mid);
+    if (s.tile) return dtype == STMOE_BF16 ? launch_tile<true>(a, st, ev_mid) : launch_tile<false>(a, st, ev_mid);
     return dtype == STMOE_BF16 ? launch_gemv_b<true>(a, s, st, ev_mid)
                                : launch_gemv_b<false>(a, s, st, ev_mid);
 }
@@ -1812,12 +1799,13 @@ extern "C" int moe_expert_ffn(const void* x, const int32_t* topk_idx, const floa
     STMOE_CHECK((reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(ws) & 255) == 0,
                 "x must be 16-byte and ws 256-byte aligned");
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y,
-                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0);
+                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0);
 }
 
 namespace {
 
-constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;
+// 16 MiB of activations and partial sums, and the slot plan behind them
+constexpr size_t kNoAllocScratchBytes = (size_t(16) << 20) + kSlotListBytes;
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices];      // device address of `scratch` per device (null until resolved)
@@ -1865,5 +1853,5 @@ extern "C" int moe_expert_ffn_noalloc(const void* x, const int32_t* topk_idx, co
     void* ws = nullptr;
     if (int rc = noalloc_scratch(&ws)) return rc;
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y, ws,
-                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0);
+                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0);
 }

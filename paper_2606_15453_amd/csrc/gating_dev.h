@@ -98,121 +98,141 @@ __device__ void expert_logits(const RouteArgs& a, float (*part)[kThreads / 64]) 
     }
 }
 
-// Softmax and top-K of every batch row in one workgroup, in three steps
-// that share LDS buffers passed by the caller (rows of `row` >= E rounded up
-// to 4 entries):
-//   stage_keys   logits -> order keys and values in LDS
-//   rank_winners for each (row, expert) pair, T lanes split the row and count
-//                the experts that beat it (larger key, or equal key and lower
-//                index): a count below K is its output position, so the
-//                selection comes out ordered (logit desc, index asc) with no
-//                serial rounds; the winner at position 0 gives the row max
-//   row_weights  one wave per row: softmax sum and the K weights.
-// The router tail and the expert FFN's routing prologue both run these, so
-// their selections and weights are bit-identical.
+constexpr int kCountMaxE = 32;
 
-// Keys padded with 0 up to a multiple of 4: a pad never beats a real key
-// and never ties with a lower index.  Ends with a barrier.
-__device__ void stage_keys(const float* z, int B, int E, int row, uint32_t* keys, float* zl) {
-    const int E4 = (E + 3) & ~3;
-    for (int i = threadIdx.x; i < B * E4; i += kThreads) {
-        const int b = i / E4, f = i - b * E4;
-        const float v = f < E ? z[b * E + f] : 0.f;
-        keys[b * row + f] = f < E ? order_key(v) : 0u;
-        zl[b * row + f] = v;
-    }
-    __syncthreads();
-}
-
-// win [B][K]: selected experts by position; rowmax [B].  Ends with a barrier.
-// The scan counts greater and equal keys (four row entries per LDS read,
-// four reads in flight); only a lane that met an equal key other than its
-// own rescans its row for equal keys at lower indices.
-__device__ void rank_winners(const uint32_t* keys, const float* zl, int B, int E, int K, int row,
-                             int32_t* win, float* rowmax) {
-    const int tid = threadIdx.x, BE = B * E;
-    int T = 1;                                    // lanes per pair (power of two)
-    while (T < 16 && BE * T * 2 <= kThreads) T *= 2;
-    const int n4 = ((E + 3) & ~3) / 4;
-    for (int base = 0; base < BE * T; base += kThreads) {
-        const int t = base + tid, i = t / T, part = t & (T - 1);
-        const int b = i / E, f = i - b * E;
-        int gt = 0, eq = 0;
-        const uint32_t* rk = keys + b * row;
-        const uint32_t mine = i < BE ? rk[f] : 0u;
-        if (i < BE) {
-            int c = part;
-            for (; c + 3 * T < n4; c += 4 * T) {
-                uint4 k[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) k[u] = *reinterpret_cast<const uint4*>(rk + 4 * (c + u * T));
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    gt += int(k[u].x > mine) + int(k[u].y > mine) + int(k[u].z > mine) + int(k[u].w > mine);
-                    eq += int(k[u].x == mine) + int(k[u].y == mine) + int(k[u].z == mine) + int(k[u].w == mine);
-                }
-            }
-            for (; c < n4; c += T) {
-                const uint4 k = *reinterpret_cast<const uint4*>(rk + 4 * c);
-                gt += int(k.x > mine) + int(k.y > mine) + int(k.z > mine) + int(k.w > mine);
-                eq += int(k.x == mine) + int(k.y == mine) + int(k.z == mine) + int(k.w == mine);
-            }
-        }
-        for (int o = 1; o < T; o <<= 1) {
-            gt += __shfl_xor(gt, o, 64);
-            eq += __shfl_xor(eq, o, 64);
-        }
-        if (i < BE && part == 0) {
-            int cnt = gt;
-            if (eq > 1)                           // ties: equal keys at lower indices rank higher
-                for (int g = 0; g < f; ++g) cnt += rk[g] == mine;
-            if (cnt < K) {
-                win[b * K + cnt] = f;
-                if (cnt == 0) rowmax[b] = zl[b * row + f];
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// Softmax weights of the winners (NaN-free logits assumed): lanes k < K of
-// the row's wave get (expert, weight) of position k.  Whole wave calls it.
-__device__ __forceinline__ void row_weights(const float* zl, const int32_t* win, const float* rowmax, int b,
-                                            int E, int K, int row, int renorm, int& e, float& wt) {
+// Softmax and top-K of one batch row by one wave, in registers: lane l holds
+// the logits l, l + 64, ... (E <= 256).  Up to kCountMaxE experts each counts
+// the ones that beat it; beyond, the K-th largest order key is found
+// bit by bit, the largest first: a ballot counts the experts whose key reaches
+// the candidate, and the search ends as soon as exactly K do (always for
+// distinct keys; equal keys that straddle the K-th place are taken at the
+// lower expert indices).  The winners then count each other for their
+// positions (logit desc, index asc).  The router tail and the expert FFN's
+// routing prologue both run this, so their selections and weights are
+// bit-identical.  Each wave works alone: no barrier.
+//
+// z [E] (global or LDS); sel [K], prob [K]: this row's, in LDS.  Lanes k < K
+// return the expert and weight of position k; sel/prob hold them as well.
+// Weights assume NaN-free logits (NaN ranks below every number).
+__device__ __forceinline__ void route_row(const float* z, int E, int K, int renorm, int32_t* sel, float* prob, int& e,
+                                          float& wt) {
+    constexpr int V = kMaxE / 64;
     const int lane = threadIdx.x & 63;
-    const float m = rowmax[b];
+    float zv[V];
+    uint32_t key[V];
+    bool ok[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int f = 64 * v + lane;
+        ok[v] = f < E;
+        zv[v] = ok[v] ? z[f] : 0.f;
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) key[v] = ok[v] ? order_key(zv[v]) : 0u;
+    bool win[V];
+    int pos[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        win[v] = false;
+        pos[v] = 0;
+    }
+    if (E <= kCountMaxE) {
+        // few experts: each counts all that beat it (its position)
+#pragma unroll 8
+        for (int g = 0; g < E; ++g) {
+            const uint32_t kg = uint32_t(__builtin_amdgcn_readlane(int(key[0]), g));
+            pos[0] += kg > key[0] || (kg == key[0] && g < lane);
+        }
+        win[0] = ok[0] && pos[0] < K;
+    } else {
+        // p: the largest value that at least K keys reach
+        uint32_t p = 0u;
+        int reach = E;
+        for (int bit = 31; bit >= 0 && reach != K; --bit) {
+            const uint32_t cand = p | (1u << bit);
+            int n = 0;
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (64 * v < E) n += __popcll(__ballot(key[v] >= cand));   // a padding key (0) reaches no candidate
+            if (n >= K) {
+                p = cand;
+                reach = n;
+            }
+        }
+        if (reach == K) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) win[v] = ok[v] && key[v] >= p;
+        } else {
+            // more than K keys reach p, the K-th largest: keys above it win, then equal ones by index
+            int above = 0, tied = 0;
+#pragma unroll
+            for (int v = 0; v < V; ++v) above += __popcll(__ballot(ok[v] && key[v] > p));
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const bool tie = ok[v] && key[v] == p;
+                const unsigned long long tm = __ballot(tie);
+                win[v] = ok[v] && (key[v] > p || (tie && above + tied + __popcll(tm & ((1ull << lane) - 1ull)) < K));
+                tied += __popcll(tm);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            unsigned long long m = __ballot(win[v]);
+            while (m) {
+                const int l = __ffsll(m) - 1, g = 64 * v + l;
+                m &= m - 1ull;
+                const uint32_t kg = uint32_t(__builtin_amdgcn_readlane(int(key[v]), l));
+#pragma unroll
+                for (int u = 0; u < V; ++u)
+                    if (64 * u < E) pos[u] += kg > key[u] || (kg == key[u] && g < 64 * u + lane);
+            }
+        }
+    }
+    // the row max is the logit of the position-0 winner
+    float m = 0.f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const unsigned long long t = __ballot(win[v] && pos[v] == 0);
+        if (t) m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zv[v]), __ffsll(t) - 1));
+        if (win[v]) {
+            sel[pos[v]] = 64 * v + lane;
+            prob[pos[v]] = zv[v];
+        }
+    }
     float s = 0.f;
-    for (int f = lane; f < E; f += 64) s += expf(zl[b * row + f] - m);
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        if (ok[v]) s += expf(zv[v] - m);
     s = wave_sum(s);
-    float p = 0.f;
+    // a wave's LDS accesses complete in order: position k's expert and logit
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    float pk = 0.f;
     e = 0;
     if (lane < K) {
-        e = win[b * K + lane];
-        p = expf(zl[b * row + e] - m) / s;
+        e = sel[lane];
+        pk = expf(prob[lane] - m) / s;
     }
-    const float wsum = wave_sum(p);
-    wt = renorm ? p / wsum : p;
+    const float wsum = wave_sum(pk);
+    wt = renorm ? pk / wsum : pk;
+    if (lane < K) prob[lane] = wt;
 }
 
-// The router tail: writes idx/w (and the selection to s_idx in LDS when
-// given) and ends with a barrier.
+// The router tail, one wave per batch row: writes idx/w (and leaves the
+// selection in LDS, s_idx [B][K], when given).  Ends with a barrier.
+template <int T>
 __device__ void softmax_topk_tail(const RouteArgs& a, const float* z, int32_t* s_idx) {
-    constexpr int kRow = kMaxE;
-    __shared__ __align__(16) uint32_t keys[kMaxB * kRow];
-    __shared__ float zl[kMaxB * kRow];
-    __shared__ int32_t win[kMaxB * kMaxK];
-    __shared__ float rowmax[kMaxB];
+    __shared__ int32_t own[kMaxB * kMaxK];
+    __shared__ float prob[kMaxB * kMaxK];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    stage_keys(z, a.B, a.E, kRow, keys, zl);
-    rank_winners(keys, zl, a.B, a.E, a.K, kRow, win, rowmax);
-    for (int b = wave; b < a.B; b += kThreads / 64) {
+    int32_t* sel = s_idx ? s_idx : own;
+    for (int b = wave; b < a.B; b += T / 64) {
         int e;
         float wt;
-        row_weights(zl, win, rowmax, b, a.E, a.K, kRow, a.renorm, e, wt);
+        route_row(z + size_t(b) * a.E, a.E, a.K, a.renorm, sel + b * a.K, prob + b * a.K, e, wt);
         if (lane < a.K) {
             a.idx[b * a.K + lane] = e;
             a.w[b * a.K + lane] = wt;
-            if (s_idx) s_idx[b * a.K + lane] = e;
         }
     }
     __syncthreads();

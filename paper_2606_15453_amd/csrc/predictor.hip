@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void route_update_predict_kernel(gating::
     n += update_segs(u, sh, g + n);
     n += predict_segs(p, sh, g + n);
     stage(g, n);
-    gating::softmax_topk_tail(r, sh.z, sh.sel);
+    gating::softmax_topk_tail<kThreads>(r, sh.z, sh.sel);
     update_body(u, sh);
     // with one layer the prediction reads the HT row the update just wrote
     if (p.ht_next && p.ht_next == u.ht)

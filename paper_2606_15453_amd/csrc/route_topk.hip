@@ -3,9 +3,9 @@
 // Two launches.  route_logits_kernel: one workgroup per expert row computes
 // its logits for all B tokens (256 lanes split H into 16-byte chunks, up to
 // eight tokens per round of loads, DPP wave sums, one LDS combine) into the
-// workspace.  route_tail_kernel: one workgroup per batch row ranks every
-// expert by counting the logits that beat it (value desc, index asc) and
-// forms the softmax weights of the winners.
+// workspace.  route_tail_kernel: one wave per batch row selects the K largest
+// (value desc, index asc) in registers and forms the softmax weights of the
+// winners.
 #include "gating_dev.h"
 
 namespace stmoe {
@@ -31,16 +31,16 @@ void launch_logits(const RouteArgs& a, hipStream_t s) {
         hipLaunchKernelGGL((route_logits_kernel<BF16, 4>), dim3(a.E, (a.B + 3) / 4), dim3(kThreads), 0, s, a);
 }
 
-// One workgroup per batch row (blockIdx.x): the tail's steps on that row
-// alone.  Ranking, softmax sum and weights of a row do not depend on the
-// other rows, so the results equal a one-workgroup tail over all rows.
-__global__ __launch_bounds__(kThreads) void route_tail_kernel(RouteArgs a) {
+// One wave per batch row (blockIdx.x): the rows' chains run side by side on
+// as many CUs.  A row does not depend on the others, so the results equal a
+// one-workgroup tail over all rows.
+__global__ __launch_bounds__(64) void route_tail_kernel(RouteArgs a) {
     const int b = blockIdx.x;
     RouteArgs r = a;
     r.B = 1;
     r.idx = a.idx + size_t(b) * a.K;
     r.w = a.w + size_t(b) * a.K;
-    softmax_topk_tail(r, a.zbuf + size_t(b) * a.E, nullptr);
+    softmax_topk_tail<64>(r, a.zbuf + size_t(b) * a.E, nullptr);
 }
 
 }  // namespace
@@ -95,7 +95,7 @@ extern "C" int moe_route_topk(const void* x, const void* w_gate, int B, int H, i
     a.logits = logits;
     a.zbuf = reinterpret_cast<float*>(ws);
     if (int rc = launch_route_logits(a, as_stream(stream))) return rc;
-    hipLaunchKernelGGL(route_tail_kernel, dim3(B), dim3(kThreads), 0, as_stream(stream), a);
+    hipLaunchKernelGGL(route_tail_kernel, dim3(B), dim3(64), 0, as_stream(stream), a);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }

@@ -206,6 +206,30 @@ def test_decode_resident_matches_oracle(name, over):
     assert np.array_equal(stats[:, 2], ref["npred"].sum(axis=0))
 
 
+@pytest.mark.parametrize("over", [dict(E=65, K=2, B=2, T=2, P=2, C=10), dict(E=64, K=4, B=5, n_shared=1, T=2, P=2, C=20),
+                                  dict(E=40, K=3, B=8, T=2, P=2, C=20, dtype="bf16"),
+                                  dict(E=64, K=4, B=9, T=2, P=2, C=40, dtype="bf16"),
+                                  dict(E=24, K=6, B=16, T=2, P=2, C=24, n_shared=2, dtype="bf16"),
+                                  dict(E=256, K=16, B=16, T=1, P=2, C=200, dtype="bf16")])
+def test_decode_plan_from_the_router_tail(over):
+    """Beyond B*E = 128 a resident layer's router tail also builds the FFN's
+    slot plan; the capped run hands the FFN the selection instead and builds
+    it there.  Both give the oracle's selections and the same bits."""
+    from oracle.stmoe_oracle import MODE_STMOE
+    from paper_2606_15453_amd import workload as W
+    cfg = W.CONFIGS["tiny"].scaled(**over)
+    st = Stack(cfg)
+    ref = _oracle(st, MODE_STMOE, ffn_tokens=0)
+    assert cfg.B * cfg.E > 128
+    a = _run_gpu(st, 1, capped=False)
+    b = _run_gpu(st, 1, capped=True)
+    for t in range(cfg.T):
+        for l in range(cfg.L):
+            for r in range(cfg.B):
+                assert sorted(a[0][t][l][r].tolist()) == sorted(ref["idx"][t * cfg.L + l][r].tolist())
+            assert np.array_equal(a[1][t][l], b[1][t][l]), (t, l)
+
+
 @pytest.mark.parametrize("over,renorm", [(dict(E=7, K=3, B=2, T=6, P=3), False),
                                          (dict(E=64, K=4, B=4, T=4, P=2, C=16), False),
                                          (dict(B=3, T=6, P=3), True),

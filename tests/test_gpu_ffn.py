@@ -175,3 +175,64 @@ def test_ffn_repeated_and_out_of_range_entries(name, row):
         print(f"{name} B={B} row {row}: rel L2 against the oracle on {len(keep)} entries {err:.3e}")
         assert np.isfinite(got).all() and err <= TOL
 
+
+
+@pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype", [
+    (2, 1, 3, 8, 8, 0, "bf16"),          # one chunk per row: the columns' remainder is all there is
+    (3, 2, 60, 136, 24, 1, "bf16"),      # one full step and a remainder, rows not a multiple of a wave's
+    (4, 6, 64, 2048, 1408, 2, "bf16"),   # split columns, no remainder, two row quads per down wave
+    (5, 3, 10, 1032, 40, 0, "f32"),      # fp32, two token groups, remainder of two chunks
+    (6, 4, 60, 2056, 1000, 1, "bf16"),   # 257 pairs of row quads: one quad per down wave
+    (8, 8, 128, 2048, 768, 0, "bf16"),   # the largest batch of two token groups
+    (8, 8, 8, 256, 64, 0, "f32"),        # every token in every slot: both token groups full
+    (9, 1, 1, 72, 104, 0, "bf16"),       # one expert serves nine tokens: four token groups
+    (14, 1, 26, 704, 2192, 0, "bf16"),   # batch beyond 8 with sizes the 16-row tiles do not take
+    (16, 2, 5, 64, 8, 8, "f32"),         # the largest batch, eight shared experts
+    (16, 16, 256, 128, 64, 0, "bf16"),   # the largest K and E: 16-row down after 4-row gate/up
+    (16, 4, 8, 128, 64, 0, "bf16"),      # many tokens per slot: 16-row gate/up
+])
+def test_ffn_tile_edges(B, K, E, H, I, n_shared, dtype):
+    """The 4-row tile kernels at the edges of their tiles, token groups and
+    splits.  fp32: the oracle's fp64 result within 1e-5 (sums of at most
+    2064 products, errors of a few fp32 roundings, 6e-8 each, per chained sum
+    of at most 64); bf16: weights and inputs are exact, activations rounded to
+    bf16 (2^-9 each)."""
+    from paper_2606_15453_amd import workload as W
+    base = W.CONFIGS["tiny" if dtype == "f32" else "qwen30b"]
+    cfg = base.scaled(H=H, I=I, E=E, K=K, B=B, dtype=dtype)
+    idx, w, x = _inputs(cfg, B, K, seed=B * 100 + H + I)
+    got, ref, err = _run_ffn(cfg, 1, idx, w, x, n_shared=n_shared)
+    print(f"B={B} K={K} E={E} H={H} I={I} +{n_shared} {dtype}: rel L2 {err:.3e}")
+    assert np.isfinite(got).all()
+    assert err <= (1e-5 if dtype == "f32" else TOL)
+
+
+@pytest.mark.parametrize("B,dtype,H,I", [(3, "bf16", 264, 72), (6, "f32", 264, 72), (7, "bf16", 256, 128)])
+def test_ffn_non_finite_weights_stay_with_their_tokens(B, dtype, H, I):
+    """An expert whose W_down holds an infinity (or whose W_gate holds a NaN)
+    changes only the rows routed to it, also where its tile serves other rows
+    beside them."""
+    import torch
+    from gpuhelp import DEV, blob_dev, i32, ptr_array, storage_dtype, to_dev
+    from paper_2606_15453_amd import stmoe as S
+    from paper_2606_15453_amd import workload as W
+    base = W.CONFIGS["tiny" if dtype == "f32" else "qwen30b"]
+    cfg = base.scaled(H=H, I=I, E=6, K=2, B=B, dtype=dtype)
+    _, w, x = _inputs(cfg, B, 2, seed=3)
+    idx = np.array([[b % 3, 3 + b % 3] for b in range(B)], np.int32)      # expert 0: rows 0, 3, 6
+    ys = []
+    for bad in (False, True):
+        blobs = [blob_dev(cfg, 0, e) for e in range(cfg.E)]
+        if bad:
+            blobs[0][2 * H * I:].fill_(float("inf"))
+            blobs[4][:H].fill_(float("nan"))                              # expert 4: rows 1, 4
+        y = torch.empty((B, H), dtype=torch.float32, device=DEV)
+        ws = torch.zeros(S.ffn_workspace_bytes(B, 2, 6, H, I, 0, storage_dtype(cfg)), dtype=torch.uint8, device=DEV)
+        S.expert_ffn(to_dev(x), i32(idx), torch.from_numpy(w).to(DEV), H, I, 6, storage_dtype(cfg),
+                     ptr_array([b.data_ptr() for b in blobs]), y, ws)
+        ys.append(y.cpu().numpy())
+    for b in range(B):
+        if b % 3 == 2:
+            assert np.array_equal(ys[0][b], ys[1][b]), b
+        else:
+            assert not np.isfinite(ys[1][b]).any(), b
