@@ -3,10 +3,10 @@
 //
 // Tables live in HBM and are small (for 94 layers x 128 experts x top-8:
 // 94 KB of CCT indices and 94 KB of confidences), so the runtime kernels run
-// as a single workgroup each: the update of one batch row touches K entries
-// x K slots (at most 256 lanes, one lane per slot), and the prediction sums
-// K x K contributions into per-row score bins in LDS with integer atomics,
-// which is exact and order-free.
+// as a single workgroup each: the update gives every selected expert's entry
+// a lane group, one lane per slot, and the prediction sums K x K contributions
+// into per-row score bins in LDS with integer atomics, which is exact and
+// order-free.
 #include <algorithm>
 #include <vector>
 
@@ -18,6 +18,8 @@ namespace stmoe {
 namespace {
 
 using namespace pred;
+
+constexpr int kThreads = 256;    // of the profiling kernels and the decode path's
 
 // ---------------------------------------------------------------- profiling
 // Algorithm 1, counting: one workgroup per (profiling token, layer pair).
@@ -70,25 +72,29 @@ __global__ __launch_bounds__(kThreads) void ht_init_kernel(const int32_t* sel_la
 }
 
 // ------------------------------------------------------ update and predict
-__global__ __launch_bounds__(kThreads) void update_kernel(UpdateArgs a) {
+template <int T>
+__global__ __launch_bounds__(T) void update_kernel(UpdateArgs a) {
     __shared__ TableShared sh;
     Seg g[kMaxSegs];
-    stage(g, update_segs(a, sh, g));
-    update_body(a, sh);
+    update_init<T>(sh);
+    stage<T>(g, update_segs(a, sh, g));
+    update_body<T>(a, sh);
 }
 
-__global__ __launch_bounds__(kThreads) void predict_kernel(PredictArgs a) {
+template <int T>
+__global__ __launch_bounds__(T) void predict_kernel(PredictArgs a) {
     __shared__ TableShared sh;
     Seg g[kMaxSegs];
-    stage(g, predict_segs(a, sh, g));
-    predict_body(a, sh);
+    stage<T>(g, predict_segs(a, sh, g));
+    predict_body<T>(a, sh);
 }
 
 // The decode path's router tail, verify/update and next-layer prediction in
 // one workgroup (after the router's logits launch).  One round of loads
 // brings the logits and every table into LDS; softmax/top-K writes the
 // selection there, and the update and the prediction run on it.
-__global__ __launch_bounds__(kThreads) void route_update_predict_kernel(gating::RouteArgs r, UpdateArgs u,
+template <int T>
+__global__ __launch_bounds__(T) void route_update_predict_kernel(gating::RouteArgs r, UpdateArgs u,
                                                                         PredictArgs p) {
     __shared__ TableShared sh;
     Seg g[kMaxSegs];
@@ -96,35 +102,38 @@ __global__ __launch_bounds__(kThreads) void route_update_predict_kernel(gating::
     p.sel_cur = nullptr;
     int n = 0;
     g[n++] = seg(r.zbuf, sh.z, size_t(r.B) * r.E * sizeof(float));
+    update_init<T>(sh);
     n += update_segs(u, sh, g + n);
     n += predict_segs(p, sh, g + n);
-    stage(g, n);
-    gating::softmax_topk_tail<kThreads>(r, sh.z, sh.sel);
-    update_body(u, sh);
+    stage<T>(g, n);
+    gating::softmax_topk_tail<T>(r, sh.z, sh.sel);
+    update_body<T>(u, sh);
     // with one layer the prediction reads the HT row the update just wrote
     if (p.ht_next && p.ht_next == u.ht)
-        for (int i = threadIdx.x; i < r.B * r.K; i += kThreads) sh.htn[i] = sh.htnew[i];
+        for (int i = threadIdx.x; i < r.B * r.K; i += T) sh.htn[i] = sh.htnew[i];
     __syncthreads();
-    predict_body(p, sh);
+    predict_body<T>(p, sh);
 }
 
 // The decode path's verify/update and next-layer prediction without the
 // router (the selection is read from global memory): used where the router
 // runs as its own launches and this work overlaps the expert FFN.
-__global__ __launch_bounds__(kThreads) void update_predict_kernel(UpdateArgs u, PredictArgs p) {
+template <int T>
+__global__ __launch_bounds__(T) void update_predict_kernel(UpdateArgs u, PredictArgs p) {
     __shared__ TableShared sh;
     Seg g[kMaxSegs];
     p.sel_cur = nullptr;     // the update's copy of the selection serves both
     int n = 0;
+    update_init<T>(sh);
     n += update_segs(u, sh, g + n);
     n += predict_segs(p, sh, g + n);
-    stage(g, n);
-    update_body(u, sh);
+    stage<T>(g, n);
+    update_body<T>(u, sh);
     // with one layer the prediction reads the HT row the update just wrote
     if (p.ht_next && p.ht_next == u.ht)
-        for (int i = threadIdx.x; i < u.B * u.K; i += kThreads) sh.htn[i] = sh.htnew[i];
+        for (int i = threadIdx.x; i < u.B * u.K; i += T) sh.htn[i] = sh.htnew[i];
     __syncthreads();
-    predict_body(p, sh);
+    predict_body<T>(p, sh);
 }
 
 // One layer's arguments of the sequential kernel below.
@@ -140,7 +149,8 @@ struct UpdPred {
 // them.
 // The arguments are built for both prediction sources with the online
 // update on; `use` and `online` select the ablation at launch time.
-__global__ __launch_bounds__(kThreads) void update_predict_seq_kernel(const UpdPred* args, int n, int use,
+template <int T>
+__global__ __launch_bounds__(T) void update_predict_seq_kernel(const UpdPred* args, int n, int use,
                                                                       int online) {
     __shared__ TableShared sh;
     for (int l = 0; l < n; ++l) {
@@ -155,17 +165,25 @@ __global__ __launch_bounds__(kThreads) void update_predict_seq_kernel(const UpdP
         Seg g[kMaxSegs];
         p.sel_cur = nullptr;     // the update's copy of the selection serves both
         int k = 0;
+        update_init<T>(sh);
         k += update_segs(u, sh, g + k);
         k += predict_segs(p, sh, g + k);
-        stage(g, k);
-        update_body(u, sh);
+        stage<T>(g, k);
+        update_body<T>(u, sh);
         if (p.ht_next && p.ht_next == u.ht)
-            for (int i = threadIdx.x; i < u.B * u.K; i += kThreads) sh.htn[i] = sh.htnew[i];
+            for (int i = threadIdx.x; i < u.B * u.K; i += T) sh.htn[i] = sh.htnew[i];
         __syncthreads();
-        predict_body(p, sh);
+        predict_body<T>(p, sh);
         __syncthreads();
     }
 }
+
+// Launch a standalone predictor kernel with the threads its shape takes.
+#define STMOE_PRED_LAUNCH(kernel, B, K, stream, args)                                             \
+    do {                                                                                          \
+        if (wide(B, K)) hipLaunchKernelGGL((kernel<1024>), dim3(1), dim3(1024), 0, stream, args); \
+        else hipLaunchKernelGGL((kernel<256>), dim3(1), dim3(256), 0, stream, args);              \
+    } while (0)
 
 int check_sel_host(const int32_t* sel, size_t rows, int E, int K) {
     for (size_t r = 0; r < rows; ++r) {
@@ -319,7 +337,7 @@ extern "C" int stmoe_update(stmoe_predictor* p, int layer, const int32_t* sel_pr
         return STMOE_ESTATE;
     }
     const UpdateArgs a = update_args(p, layer, sel_prev, sel_cur, online);
-    hipLaunchKernelGGL(update_kernel, dim3(1), dim3(kThreads), 0, as_stream(stream), a);
+    STMOE_PRED_LAUNCH(update_kernel, p->B, p->K, as_stream(stream), a);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
@@ -338,7 +356,7 @@ extern "C" int stmoe_predict(stmoe_predictor* p, int layer, const int32_t* sel_c
         return STMOE_ESTATE;
     }
     const PredictArgs a = predict_args(p, layer, sel_cur, use, score, mask, max_score, ranked, n_ranked);
-    hipLaunchKernelGGL(predict_kernel, dim3(1), dim3(kThreads), 0, as_stream(stream), a);
+    STMOE_PRED_LAUNCH(predict_kernel, p->B, p->K, as_stream(stream), a);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
@@ -377,7 +395,7 @@ int fused_route_predict(const void* x, const void* w_gate, int H, int dtype, int
                               : predict_args(p, -1, nullptr, use & STMOE_USE_HT, nullptr, nullptr, max_score,
                                              ranked, n_ranked);
     if (int rc = launch_route_logits(r, s)) return rc;
-    hipLaunchKernelGGL(route_update_predict_kernel, dim3(1), dim3(kThreads), 0, s, r, u, q);
+    hipLaunchKernelGGL((route_update_predict_kernel<kThreads>), dim3(1), dim3(kThreads), 0, s, r, u, q);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
@@ -468,7 +486,7 @@ int update_predict(stmoe_predictor* p, int layer, const int32_t* sel_prev, const
                               ? predict_args(p, layer, sel_cur, use, nullptr, nullptr, max_score, ranked, n_ranked)
                               : predict_args(p, -1, nullptr, use & STMOE_USE_HT, nullptr, nullptr, max_score,
                                              ranked, n_ranked);
-    hipLaunchKernelGGL(update_predict_kernel, dim3(1), dim3(kThreads), 0, s, u, q);
+    hipLaunchKernelGGL((update_predict_kernel<kThreads>), dim3(1), dim3(kThreads), 0, s, u, q);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
@@ -504,7 +522,7 @@ int update_predict_seq(stmoe_predictor* p, const void* dev_args, int use, int on
         set_error("moe_decode_token: predictor has not been profiled");
         return STMOE_ESTATE;
     }
-    hipLaunchKernelGGL(update_predict_seq_kernel, dim3(1), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL((update_predict_seq_kernel<kThreads>), dim3(1), dim3(kThreads), 0, s,
                        static_cast<const UpdPred*>(dev_args), p->L, use, online ? 1 : 0);
     STMOE_LAUNCHED();
     return STMOE_OK;

@@ -2,8 +2,8 @@
 // (Algorithm 3, with the HT overwrite and the hit count of the verify step)
 // and the Expert Predict function (Algorithm 2 with Eq. 1).  Shared by the
 // standalone predictor kernels and the decode path's router + predictor
-// kernel.  Both bodies run in one 256-thread workgroup on an LDS image of
-// the tables.
+// kernel.  Both bodies run in one workgroup of T threads (256 or 1024, see
+// wide()) on an LDS image of the tables.
 #pragma once
 
 #include "common.h"
@@ -31,7 +31,7 @@ inline size_t round4(size_t n) { return (n + 3) / 4 * 4; }
 namespace stmoe {
 namespace pred {
 
-constexpr int kThreads = 256;
+constexpr int kWaveE = kMaxE / 64;   // waves that hold one expert per lane
 constexpr int kConfInit = 2;   // "10", preferred
 constexpr int kConfMax = 3;    // "11", strongly preferred
 constexpr int kThreshold = 2;  // prefetch when the score reaches "10"
@@ -67,7 +67,7 @@ struct PredictArgs {
 // in an imported entry) take an exact O(E) ranking instead.
 constexpr int kScoreBins = 64;
 static_assert(kMaxK * kConfMax + kHtScore < kScoreBins, "score histogram too small");
-static_assert(kMaxE <= kThreads, "one expert per thread in the ranking");
+static_assert(kMaxE <= 256, "one expert per thread in the ranking");
 
 // LDS image of every table one update + predict touches.  The tables are
 // small (at most E*K = 4 KB each), so each kernel copies them in with one
@@ -89,10 +89,23 @@ struct TableShared {
     __align__(16) int32_t sel[kMaxB * kMaxK];
     __align__(16) int32_t Fs[kMaxB * kMaxK];  // every row's actual set, ascending (row stride kMaxK)
     int mx[kMaxE];                    // max score over rows
-    int whist[kThreads / 64][kScoreBins];  // per-wave histogram of candidate scores
+    int whist[kWaveE][kScoreBins];    // per-wave histogram of candidate scores
     int greater[kScoreBins];          // candidates scoring above each value
+    uint32_t rows[kMaxE];             // update: rows whose previous selection holds the expert
+    uint32_t owner[kMaxE];            // ... and the first (row, position) that does
+    __align__(16) uint8_t ent[128][16];   // CCT entries under update, one per lane group
     unsigned hits, npred;
 };
+
+// Threads of the standalone update and predict launches: a lane group of 8
+// (16 for K > 8) lanes per selected expert updates its entry, so more
+// selections than 256 threads hold take 1024 (16 rows, top-8, E 128: update
+// 8.0 us against 13.2 with 256 threads and 15.7 with the rows in turn; predict
+// 4.0 against 5.1).  Fewer waves start faster, and the launches that run
+// beside the expert FFN take 256 always: a workgroup of 1024 waits for sixteen
+// free waves on one CU (Qwen3-30B shapes at batch 8, layer calls: 870 us a
+// token against 789).
+inline bool wide(int B, int K) { return B * K * (K <= 8 ? 8 : 16) > 256; }
 
 // One contiguous global -> LDS copy of n 4-byte words (null src: nothing).
 struct Seg {
@@ -110,30 +123,31 @@ __device__ __forceinline__ Seg seg(const void* src, void* dst, size_t bytes) {
 }
 
 constexpr int kMaxSegs = 10;
-constexpr int kStageRegs = 4;   // words per thread per segment in one pass
 
-// Copy every segment into LDS.  In each pass a thread loads up to
-// kStageRegs words of every segment before its first LDS store, so the whole
-// copy is one memory round trip at decode sizes.  Ends with a barrier.
+// Copy every segment into LDS.  In each pass a thread loads up to 1024 / T
+// words of every segment before its first LDS store, so the whole copy is one
+// memory round trip at decode sizes.  Ends with a barrier.
+template <int T>
 __device__ void stage(const Seg* g, int nseg) {
+    constexpr int R = 1024 / T;
     int most = 0;
 #pragma unroll
     for (int j = 0; j < kMaxSegs; ++j)
         if (j < nseg) most = max(most, g[j].n);
-    for (int base = 0; base < most; base += kThreads * kStageRegs) {
-        uint32_t val[kMaxSegs][kStageRegs];
+    for (int base = 0; base < most; base += T * R) {
+        uint32_t val[kMaxSegs][R];
 #pragma unroll
         for (int j = 0; j < kMaxSegs; ++j)
 #pragma unroll
-            for (int r = 0; r < kStageRegs; ++r) {
-                const int i = base + r * kThreads + int(threadIdx.x);
+            for (int r = 0; r < R; ++r) {
+                const int i = base + r * T + int(threadIdx.x);
                 val[j][r] = j < nseg && i < g[j].n ? g[j].src[i] : 0u;
             }
 #pragma unroll
         for (int j = 0; j < kMaxSegs; ++j)
 #pragma unroll
-            for (int r = 0; r < kStageRegs; ++r) {
-                const int i = base + r * kThreads + int(threadIdx.x);
+            for (int r = 0; r < R; ++r) {
+                const int i = base + r * T + int(threadIdx.x);
                 if (j < nseg && i < g[j].n) g[j].dst[i] = val[j][r];
             }
     }
@@ -165,92 +179,106 @@ __device__ __forceinline__ int predict_segs(const PredictArgs& a, TableShared& s
     return n;
 }
 
-// Algorithm 3 on CCT_{layer-1} for rows b = 0..B-1 in order.  Lane t of a
-// group of GS lanes (one wave holds whole groups) owns slot s = t % GS of
-// entry g = t / GS, the g-th expert of A_{layer-1}[b]; the entries of one row
-// are distinct, so the groups of a row are independent and only the order of
-// rows is serial.  Each lane reads its entry's whole snapshot with its own
-// slot (one LDS round trip per row: the next row's entry index is loaded a
-// row ahead, since the update never writes it), and the group's replaced
-// slots and absent experts meet in two ballots.  With GS = 8 (K <= 8) every
-// group sits in wave 0 and rows follow each other without a workgroup
-// barrier (a wave's LDS accesses complete in order); with GS = 16 groups
-// span the four waves and a barrier separates rows.  Loops run to GS with
-// reads that stay inside the LDS arrays, so their reads issue together.
-template <int GS>
-__device__ __forceinline__ void cct_rows(const UpdateArgs& a, TableShared& sh) {
-    constexpr bool one_wave = GS * GS <= 64;
-    const int t = threadIdx.x, K = a.K, E = a.E;
-    const int g = t / GS, s = t % GS, first = (t & 63) - s;
-    const bool on = g < K && s < K;
-    if (one_wave && t >= 64) return;
+// Algorithm 3 on CCT_{layer-1}.  The rows b = 0..B-1 update an entry one
+// after the other, but entries of different experts do not meet: the lane
+// group of an expert's first (row, position) takes every row that selected
+// it, in order, and the experts go side by side.  So the chain is as long as
+// the most popular expert has rows, not B (16 rows, top-8 of 128: about 5).
+// Lane s of a group of GS owns slot s of the entry.  Each lane reads the
+// entry's whole snapshot from the group's LDS copy (one round trip per row),
+// and the group's replaced slots and absent experts meet in two ballots.
+// Loops run to GS with reads that stay inside the LDS arrays, so their reads
+// issue together.  The owner writes the entry back to global memory.
+template <int GS, int T>
+__device__ __forceinline__ void cct_entries(const UpdateArgs& a, TableShared& sh) {
+    constexpr int groups = T / GS;
+    static_assert(groups <= 128, "one LDS entry per group");
+    const int t = threadIdx.x, K = a.K, E = a.E, BK = a.B * K;
+    const int grp = t / GS, s = t % GS, first = (t & 63) - s;
     const unsigned gmask = (1u << K) - 1u;
-    int e = on ? sh.prev[g] : -1;
-    for (int b = 0; b < a.B; ++b) {
-        const bool ok = e >= 0 && e < E;      // out-of-range selections are ignored
-        const int ec = ok ? e : 0;
-        const int32_t* F = sh.Fs + b * kMaxK;
-        const uint8_t* entry = sh.uidx + ec * K;   // + j < kMaxE * kMaxK for j < GS
-        int Fv[GS], snap[GS];
+    uint32_t* ent = reinterpret_cast<uint32_t*>(sh.ent[grp]);
+    for (int base = 0; base < BK; base += groups) {
+        const int at = base + grp;
+        const int e = at < BK ? sh.prev[at] : -1;
+        const bool ok = e >= 0 && e < E;          // out-of-range selections are ignored
+        uint32_t rows = ok && sh.owner[ok ? e : 0] == uint32_t(at) ? sh.rows[e] : 0u;
+        const bool own = rows != 0 && s < K;
+        int f = own ? sh.uidx[e * K + s] : 0;
+        int conf = own ? sh.uconf[e * K + s] : 0;
+        if (own) sh.ent[grp][s] = uint8_t(f);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        while (__any(rows != 0)) {
+            const bool on = rows != 0 && s < K;
+            const int b = rows ? __ffs(rows) - 1 : 0;
+            const int32_t* F = sh.Fs + b * kMaxK;
+            int Fv[GS];
+            uint32_t snap[GS / 4];
 #pragma unroll
-        for (int j = 0; j < GS; ++j) {
-            Fv[j] = F[j];
-            snap[j] = entry[j];
-        }
-        const int mine = F[s], f = entry[s];
-        int conf = sh.uconf[ec * K + s];
-        const int e_next = on && b + 1 < a.B ? sh.prev[(b + 1) * K + g] : -1;
-        bool hit = false, held = false;
+            for (int j = 0; j < GS; ++j) Fv[j] = F[j];
 #pragma unroll
-        for (int j = 0; j < GS; ++j) {
-            hit |= j < K && Fv[j] == f;
-            held |= j < K && snap[j] == mine;
-        }
-        // slots replaced in this entry, and experts of F absent from it
-        const unsigned long long rm = __ballot(ok && !hit && conf == 0);
-        const unsigned long long am = __ballot(on && !held);
-        if (ok) {
-            if (hit) {
-                conf = min(conf + 1, kConfMax);
-            } else if (conf > 0) {
-                conf -= 1;
-            } else {
-                // the rank-th absent expert of F (ascending), rank = replaced
-                // slots before this one
-                const int rank = __popc(unsigned(rm >> first) & gmask & ((1u << s) - 1u));
-                unsigned abs_ = unsigned(am >> first) & gmask;
+            for (int j = 0; j < GS / 4; ++j) snap[j] = ent[j];
+            const int mine = F[s];
+            bool hit = false, held = false;
 #pragma unroll
-                for (int q = 0; q < GS; ++q)
-                    if (q < rank) abs_ &= abs_ - 1u;
-                const int at = __ffs(abs_) - 1;
-                int pick = 0;
-#pragma unroll
-                for (int j = 0; j < GS; ++j) pick = j == at ? Fv[j] : pick;
-                if (abs_) sh.uidx[e * K + s] = uint8_t(pick);
-                conf = kConfInit;
+            for (int j = 0; j < GS; ++j) {
+                hit |= j < K && Fv[j] == f;
+                held |= j < K && int((snap[j / 4] >> (8 * (j & 3))) & 255u) == mine;
             }
-            sh.uconf[e * K + s] = uint8_t(conf);
+            // slots replaced in this entry, and experts of F absent from it
+            const unsigned long long rm = __ballot(on && !hit && conf == 0);
+            const unsigned long long am = __ballot(on && !held);
+            if (on) conf = hit ? min(conf + 1, kConfMax) : conf > 0 ? conf - 1 : conf;
+            if (rm) {
+                if ((rm >> (t & 63)) & 1ull) {
+                    // the rank-th absent expert of F (ascending), rank = replaced
+                    // slots before this one
+                    const int rank = __popc(unsigned(rm >> first) & gmask & ((1u << s) - 1u));
+                    unsigned abs_ = unsigned(am >> first) & gmask;
+#pragma unroll
+                    for (int q = 0; q < GS; ++q)
+                        if (q < rank) abs_ &= abs_ - 1u;
+                    const int pos = __ffs(abs_) - 1;
+                    int pick = f;
+#pragma unroll
+                    for (int j = 0; j < GS; ++j) pick = j == pos ? Fv[j] : pick;
+                    f = pick & 255;
+                    conf = kConfInit;
+                    sh.ent[grp][s] = uint8_t(f);
+                }
+                // the next row reads the entry (a wave's LDS accesses complete in order)
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+            rows &= rows - 1u;
         }
-        e = e_next;
-        // the next row may update the same entries
-        if (one_wave)
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        else
-            __syncthreads();
+        if (own) {
+            a.cidx[e * K + s] = uint8_t(f);
+            a.cconf[e * K + s] = uint8_t(conf);
+        }
     }
+}
+
+// Before the staging barrier: empty row sets.
+template <int T>
+__device__ __forceinline__ void update_init(TableShared& sh) {
+    for (int i = threadIdx.x; i < kMaxE; i += T) {
+        sh.rows[i] = 0u;
+        sh.owner[i] = ~0u;
+    }
+    if (threadIdx.x == 0) { sh.hits = 0; sh.npred = 0; }
 }
 
 // The verify step and Algorithm 3 for one layer: hits of the selection
 // against the prediction made for this layer, HT[layer][b] <- sorted
-// selection, then the CCT_{layer-1} entries of every row (cct_rows).  Works
-// on the LDS image (staged by the caller), then writes the touched CCT
-// entries, HT and the hit counts back.  Ends with a barrier.
+// selection, then the CCT_{layer-1} entries of every row (cct_entries).  Works
+// on the LDS image (staged by the caller behind update_init), writes the
+// touched CCT entries, HT and the hit counts back.  Ends with a barrier.
+template <int T>
 __device__ void update_body(const UpdateArgs& a, TableShared& sh) {
     const int tid = threadIdx.x, K = a.K, E = a.E, BK = a.B * K;
     const bool cct = a.cidx != nullptr && a.online;
     // every row sorted ascending: a lane per selected expert finds its rank
     // (reads past the last row stay inside sel: B, K <= 16)
-    for (int i = tid; i < BK; i += kThreads) {
+    for (int i = tid; i < BK; i += T) {
         const int32_t* row = sh.sel + (i / K) * K;
         const int v = sh.sel[i];
         int rank = 0;
@@ -262,68 +290,63 @@ __device__ void update_body(const UpdateArgs& a, TableShared& sh) {
         sh.Fs[(i / K) * kMaxK + rank] = v;
     }
     unsigned my_hits = 0, my_pred = 0;
-    for (int i = tid; i < BK; i += kThreads) {
+    for (int i = tid; i < BK; i += T) {
         const int v = sh.sel[i];
         if (v >= 0 && v < E) my_hits += sh.pend[(i / K) * E + v] >= kThreshold;
+        if (cct) {
+            const int e = sh.prev[i];
+            if (e >= 0 && e < E) {
+                atomicOr(&sh.rows[e], 1u << (i / K));
+                atomicMin(&sh.owner[e], unsigned(i));
+            }
+        }
     }
-    for (int i = tid; i < a.B * E; i += kThreads) my_pred += sh.pend[i] >= kThreshold;
-    if (tid == 0) { sh.hits = 0; sh.npred = 0; }
+    for (int i = tid; i < a.B * E; i += T) my_pred += sh.pend[i] >= kThreshold;
+    if (my_hits) atomicAdd(&sh.hits, my_hits);
+    if (my_pred) atomicAdd(&sh.npred, my_pred);
     __syncthreads();
-    for (int i = tid; i < BK; i += kThreads) {
+    for (int i = tid; i < BK; i += T) {
         const uint8_t v = uint8_t(sh.Fs[(i / K) * kMaxK + i % K]);
         sh.htnew[i] = v;
         a.ht[i] = v;
     }
     if (cct) {
         if (K <= 8)
-            cct_rows<8>(a, sh);
+            cct_entries<8, T>(a, sh);
         else
-            cct_rows<16>(a, sh);
+            cct_entries<16, T>(a, sh);
     }
-    __syncthreads();
-    if (cct) {
-        // write back every entry slot this layer's rows touched (duplicates
-        // carry the same final value)
-        for (int i = tid; i < a.B * K * K; i += kThreads) {
-            const int e = sh.prev[i / K], s = i % K;
-            if (e >= 0 && e < E) {
-                a.cidx[e * K + s] = sh.uidx[e * K + s];
-                a.cconf[e * K + s] = sh.uconf[e * K + s];
-            }
-        }
-    }
-    if (my_hits) atomicAdd(&sh.hits, my_hits);
-    if (my_pred) atomicAdd(&sh.npred, my_pred);
-    __syncthreads();
     if (tid == 0) {
         atomicAdd(&a.stats[0], (unsigned long long)sh.hits);
         atomicAdd(&a.stats[1], (unsigned long long)(a.B * K));
         atomicAdd(&a.stats[2], (unsigned long long)sh.npred);
     }
+    __syncthreads();
 }
 
 // Algorithm 2 with Eq. 1: score_b[f] = sum_{e in A[b]} conf of f in CCT[e]
 // + 2 [f in HT_next[b]]; PrefetchSet = {f : score >= 2}; the union over rows
 // ranked by (max score desc, index asc).  Integer atomics in LDS: exact.
 // Reads the LDS image (staged by the caller; htn holds HT[layer+1]).
+template <int T>
 __device__ void predict_body(const PredictArgs& a, TableShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int K = a.K, KK = a.K * a.K, E = a.E;
-    for (int i = tid; i < a.B * E; i += kThreads) sh.sc[i] = 0;
-    for (int i = tid; i < (kThreads / 64) * kScoreBins; i += kThreads) (&sh.whist[0][0])[i] = 0;
+    for (int i = tid; i < a.B * E; i += T) sh.sc[i] = 0;
+    for (int i = tid; i < kWaveE * kScoreBins; i += T) (&sh.whist[0][0])[i] = 0;
     __syncthreads();
     if (a.cidx) {
-        for (int i = tid; i < a.B * KK; i += kThreads) {
+        for (int i = tid; i < a.B * KK; i += T) {
             const int b = i / KK, e = sh.sel[b * K + (i % KK) / K], s = i % K;
             const int f = e >= 0 && e < E ? sh.pidx[e * K + s] : E;
             if (f < E) atomicAdd(&sh.sc[b * E + f], int(sh.pconf[e * K + s]));
         }
     }
     if (a.ht_next)
-        for (int i = tid; i < a.B * K; i += kThreads)
+        for (int i = tid; i < a.B * K; i += T)
             if (sh.htn[i] < E) atomicAdd(&sh.sc[(i / K) * E + sh.htn[i]], kHtScore);
     __syncthreads();
-    for (int i = tid; i < a.B * E; i += kThreads) {
+    for (int i = tid; i < a.B * E; i += T) {
         a.pend[i] = uint8_t(sh.sc[i]);
         if (a.score) a.score[i] = uint8_t(sh.sc[i]);
     }
@@ -363,7 +386,7 @@ __device__ void predict_body(const PredictArgs& a, TableShared& sh) {
         // greater[t] = candidates with score > t: suffix sum of the histogram
         int h = 0;
 #pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) h += sh.whist[w][lane];
+        for (int w = 0; w < kWaveE; ++w) h += sh.whist[w][lane];
         int suf = h;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -387,7 +410,7 @@ __device__ void predict_body(const PredictArgs& a, TableShared& sh) {
         if (cand) {
             int rank = sh.greater[m] + __popcll(same & ((1ull << lane) - 1ull));
 #pragma unroll
-            for (int w = 0; w < kThreads / 64; ++w)
+            for (int w = 0; w < kWaveE; ++w)
                 if (w < wave) rank += sh.whist[w][m];
             a.ranked[rank] = f;
         }
