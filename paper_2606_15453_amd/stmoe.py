@@ -171,10 +171,16 @@ def _p(t):
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _s(stream):
+    """Raw handle of a torch stream / int; None: the current device's current
+    stream, looked up without building a torch.cuda.Stream on each call."""
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
