@@ -492,6 +492,10 @@ __device__ __forceinline__ int b1_routed(const FfnArgs& a, int j, float& wj, int
     return lane_i(ek, src);
 }
 
+// Slot j of the list, and its counts (SlotList is defined with its readers).
+__device__ void publish_b1_slot(const FfnArgs& a, int j, const char* blob);
+__device__ void publish_b1_counts(const FfnArgs& a, int n_routed);
+
 template <bool BF, int G, int R>
 __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks_per_slot, int act16) {
     constexpr int esz = BF ? 2 : 4;
@@ -503,6 +507,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
     float wj = 1.f;
     int n_routed = 0;
     const int e = a.logits ? b1_routed(a, j, wj, n_routed, sel[wave], prob[wave]) : b1_given(a, j, wj, n_routed);
+    // the slot list for the down launch (its counts also when no slot is selected)
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish_b1_counts(a, n_routed);
     const char* blob;
     if (e >= 0) {
         blob = routed_blob(a, e);
@@ -512,6 +518,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
     } else {
         return;
     }
+    if (threadIdx.x == 0 && blockIdx.x % blocks_per_slot == 0) publish_b1_slot(a, j, blob);
     const int grp = lane / G, g = lane % G;
     const int i0 = (blockIdx.x % blocks_per_slot) * (kWaves * (64 / G) * R) + (wave * (64 / G) + grp) * R;
     if (i0 >= a.I) return;   // I is a multiple of R
@@ -575,6 +582,15 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
 }
 
 #include "ffn_tile.h"
+
+// The slots of a GEMV down workgroup: at batch 1 from the list the gate/up
+// launch leaves (one round of loads and one barrier; Qwen3-30B shapes, batch
+// 1), beyond rebuilt from the selection.
+template <int NB>
+using DownPlan = typename std::conditional<NB == 1, SlotTable, PlanB>::type;
+__device__ __forceinline__ void down_plan(const FfnArgs& a, SlotTable& p) { load_slots(a, p); }
+__device__ __forceinline__ void down_plan(const FfnArgs& a, PlanB& p) { build_plan(a, p); }
+__device__ __forceinline__ const char* slot_blob(const FfnArgs&, const SlotTable& p, int j) { return p.blob[j]; }
 
 // One slot's contribution to R down rows: chunk steps c0, c0 + S, ... of
 // the rows, U steps in flight.  With CARRY the activation chunks of the
@@ -748,9 +764,9 @@ __device__ __forceinline__ void down_slot16(const char* wd, size_t rowb, int cpr
 template <bool BF, int G, int R, int NB, int U>
 __global__ __launch_bounds__(kThreads) void ffn_down_rows(FfnArgs a) {
     constexpr int kRows = (64 / G) * R;
-    __shared__ PlanB p;
+    __shared__ DownPlan<NB> p;
     __shared__ float red[kWaves][kRows][NB];
-    build_plan(a, p);
+    down_plan(a, p);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lg = lane / G, g = lane % G;
     const int hb = blockIdx.x * kRows;
@@ -803,9 +819,9 @@ __global__ __launch_bounds__(kThreads) void ffn_down_rows(FfnArgs a) {
 // through LDS.
 template <bool BF, int R, int NB>
 __global__ __launch_bounds__(kThreads) void ffn_down_wg(FfnArgs a) {
-    __shared__ PlanB p;
+    __shared__ DownPlan<NB> p;
     __shared__ float red[kWaves][R][NB];
-    build_plan(a, p);
+    down_plan(a, p);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h0 = blockIdx.x * R;   // H is a multiple of R
     if (blockIdx.x == 0 && tid == 0 && a.n_experts)

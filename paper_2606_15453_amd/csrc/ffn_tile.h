@@ -77,6 +77,15 @@ struct SlotList {
     SlotRec rec[kMaxSlots];
 };
 
+__device__ void publish_b1_slot(const FfnArgs& a, int j, const char* blob) {
+    a.slots->rec[j].blob = blob;
+    a.slots->rec[j].tok = 1u;
+}
+__device__ void publish_b1_counts(const FfnArgs& a, int n_routed) {
+    a.slots->n_routed = n_routed;
+    a.slots->n_slots = n_routed + a.n_shared;
+}
+
 // One workgroup of T threads: build the plan of a selection in LDS (idx, w
 // [B][K]; entries outside [0, E) are ignored, a repeated expert counts once,
 // with its first entry's weight).
