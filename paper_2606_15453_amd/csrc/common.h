@@ -52,6 +52,13 @@ constexpr int kMaxH = 16384;
 // separate router tail costs less than the larger prologue)
 constexpr int kRouteInFfnMax = 128;
 
+// router bytes (E rows of H) up to which the batch-1 gate/up kernel computes
+// the logits too: every workgroup reads the whole router, and a launch less is
+// worth more where that is one or two loads per lane (E 8, H 256 fp32, 8 KiB:
+// 15.9 us a layer with the router launch); only while the grid is one
+// round of workgroups
+constexpr int kRouterInFfnBytes = 16384;
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }

@@ -22,7 +22,8 @@ namespace stmoe {
 int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
                int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
                float* y, void* ws, hipStream_t s, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride, int ready);
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router);
+bool ffn_takes_router(int B, int K, int H, int I, int E, int n_shared, int dtype);
 bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype);
 int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
                    const void* const* eptr, const void* const* sptr, int n_shared, void* ws, const void* ebase,
@@ -469,7 +470,11 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
     };
     if (timed)
         if (int rc = stamp_event(tl.route0, c->s)) return rc;
-    if (route_in_ffn) {
+    // a small router at batch 1: its logits, too, come from the gate/up kernel
+    const bool router_in_ffn = route_in_ffn && ffn_takes_router(B, K, c->H, c->I, E, c->n_shared, c->dtype);
+    if (router_in_ffn) {
+        // nothing to launch
+    } else if (route_in_ffn) {
         if (int rc = route_logits(x, c->router[layer], B, c->H, E, c->dtype, zbuf, c->s)) return rc;
     } else if (plan || (use && c->side)) {
         if (plan) {
@@ -557,7 +562,8 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
     if (int rc = ffn_launch(x, idx_l, w_l, B, K, c->H, c->I, E, c->dtype, c->tables + size_t(layer) * E,
                             sptr, c->n_shared,
                             y, c->ffn_ws, c->s, timed ? c->n_experts : nullptr, e1,
-                            route_in_ffn ? zbuf : nullptr, c->renorm, ebase, c->rstride, plan))
+                            route_in_ffn && !router_in_ffn ? zbuf : nullptr, c->renorm, ebase, c->rstride, plan,
+                            router_in_ffn ? c->router[layer] : nullptr))
         return rc;
     if (timed) {
         if (int rc = stamp_event(tl.down1, c->s)) return rc;

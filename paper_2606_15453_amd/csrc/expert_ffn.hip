@@ -100,6 +100,7 @@ struct FfnArgs {
     // selection to idx/w for the down kernel and the caller
     const float* logits;
     int renorm;
+    const void* router;              // batch 1: router rows [E][H], the logits computed here as well
 };
 
 struct Plan {
@@ -473,11 +474,12 @@ __device__ __forceinline__ int b1_given(const FfnArgs& a, int j, float& wj, int&
 // Router logits given: every wave routes the token in registers (the router
 // tail's row, so selection and weights are bit-identical); slot j is the j-th
 // smallest of the K winners.  Block 0 publishes idx/w.
-__device__ __forceinline__ int b1_routed(const FfnArgs& a, int j, float& wj, int& n_routed, int32_t* sel, float* prob) {
+__device__ __forceinline__ int b1_routed(const FfnArgs& a, const float* z, int j, float& wj, int& n_routed,
+                                         int32_t* sel, float* prob) {
     const int K = a.K, lane = threadIdx.x & 63;
     int ek;
     float wk;
-    gating::route_row(a.logits, a.E, K, a.renorm, sel, prob, ek, wk);
+    gating::route_row(z, a.E, K, a.renorm, sel, prob, ek, wk);
     if (blockIdx.x == 0 && threadIdx.x < K) {
         const_cast<int32_t*>(a.idx)[lane] = ek;
         const_cast<float*>(a.w)[lane] = wk;
@@ -506,7 +508,19 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
     __shared__ float prob[kWaves][kMaxK];
     float wj = 1.f;
     int n_routed = 0;
-    const int e = a.logits ? b1_routed(a, j, wj, n_routed, sel[wave], prob[wave]) : b1_given(a, j, wj, n_routed);
+    __shared__ float zs[kMaxE];
+    const float* z = a.logits;
+    if (a.router) {
+        const int chunks = a.H * esz / 16;
+        for (int x = wave; x < a.E; x += kWaves) {
+            const float v = gating::wave_logit<BF>(reinterpret_cast<const uint4*>(a.router) + size_t(x) * chunks,
+                                                   reinterpret_cast<const uint4*>(a.x), chunks);
+            if (lane == 0) zs[x] = v;
+        }
+        __syncthreads();
+        z = zs;
+    }
+    const int e = z ? b1_routed(a, z, j, wj, n_routed, sel[wave], prob[wave]) : b1_given(a, j, wj, n_routed);
     // the slot list for the down launch (its counts also when no slot is selected)
     if (blockIdx.x == 0 && threadIdx.x == 0) publish_b1_counts(a, n_routed);
     const char* blob;
@@ -1739,6 +1753,15 @@ bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype) 
     return s.mfma || s.tile;
 }
 
+// Whether the gate/up launch of these shapes can run the whole router: batch
+// 1, a small router, and one round of workgroups.
+bool ffn_takes_router(int B, int K, int H, int I, int E, int n_shared, int dtype) {
+    if (B != 1 || size_t(E) * H * (dtype == STMOE_BF16 ? 2 : 4) > size_t(kRouterInFfnBytes)) return false;
+    const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
+    const int rows = kWaves * (64 / s.gu_G);
+    return (I + rows - 1) / rows * s.slots <= 1024;
+}
+
 // The router's tail (from the logits z [B][E], writing idx/w) and the FFN's
 // slot plan, one launch.  The workspace is the FFN's.
 int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
@@ -1763,12 +1786,13 @@ int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, in
 
 // Internal entry used by the decode-layer orchestration (no argument checks).
 // With `logits` (B*E <= kRouteInFfnMax) the gate/up kernel routes first and
-// idx/w are outputs, written before the down kernel reads them.  `ready`: the
-// plan is in the workspace (ffn_route_plan on this stream).
+// idx/w are outputs, written before the down kernel reads them; `router` (where
+// ffn_takes_router says so) instead of `logits`: the same, logits included.
+// `ready`: the plan is in the workspace (ffn_route_plan on this stream).
 int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
                int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
                float* y, void* ws, hipStream_t st, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride, int ready) {
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router) {
     if (logits && B * E > kRouteInFfnMax) {
         set_error("ffn_launch: routing inside the FFN needs B*E <= 128");
         return STMOE_EINVAL;
@@ -1779,6 +1803,7 @@ int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, 
     a.logits = logits;
     a.renorm = renorm;
     a.ready = ready;
+    a.router = router;
     if (s.mfma) return launch_mfma(a, s, st, ev_mid);
     if (s.tile) return dtype == STMOE_BF16 ? launch_tile<true>(a, st, ev_mid) : launch_tile<false>(a, st, ev_mid);
     return dtype == STMOE_BF16 ? launch_gemv_b<true>(a, s, st, ev_mid)
@@ -1815,7 +1840,7 @@ extern "C" int moe_expert_ffn(const void* x, const int32_t* topk_idx, const floa
     STMOE_CHECK((reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(ws) & 255) == 0,
                 "x must be 16-byte and ws 256-byte aligned");
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y,
-                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0);
+                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr);
 }
 
 namespace {
@@ -1869,5 +1894,5 @@ extern "C" int moe_expert_ffn_noalloc(const void* x, const int32_t* topk_idx, co
     void* ws = nullptr;
     if (int rc = noalloc_scratch(&ws)) return rc;
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y, ws,
-                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0);
+                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr);
 }

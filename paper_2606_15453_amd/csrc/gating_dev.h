@@ -47,6 +47,28 @@ __device__ __forceinline__ uint32_t order_key(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// One token's logit of one expert by one wave: the steps and the order of
+// expert_logits below (its four waves' sums one after the other), so the bits
+// are the same.  For routers that fit a workgroup's prologue.
+template <bool BF16>
+__device__ __forceinline__ float wave_logit(const uint4* wrow, const uint4* x, int chunks) {
+    const int lane = threadIdx.x & 63;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    float z = 0.f;
+    for (int w = 0; w < kThreads / 64; ++w) {
+        float acc = 0.f;
+        for (int c = 64 * w + lane; c < chunks; c += 2 * kThreads) {
+            const bool two = c + kThreads < chunks;
+            const uint4 w0 = wrow[c], x0 = x[c];
+            const uint4 w1 = two ? wrow[c + kThreads] : zero, x1 = two ? x[c + kThreads] : zero;
+            dot_chunk<BF16>(w0, x0, acc);
+            if (two) dot_chunk<BF16>(w1, x1, acc);
+        }
+        z += 64 * w < chunks ? wave_sum(acc) : 0.f;
+    }
+    return z;
+}
+
 // Logits of expert row blockIdx.x for the tokens of row group blockIdx.y
 // (NB tokens per group), written to the workspace.  The 256 lanes split H
 // into 16-byte chunks, two chunks per step, and every chunk of the group's
