@@ -471,12 +471,54 @@ __device__ __forceinline__ int b1_given(const FfnArgs& a, int j, float& wj, int&
     return lane_i(v, src);
 }
 
-// Router logits given: every wave routes the token in registers (the router
-// tail's row, so selection and weights are bit-identical); slot j is the j-th
-// smallest of the K winners.  Block 0 publishes idx/w.
+// Router logits given: every wave routes the token in registers, with the
+// router tail's arithmetic (selection and weights are bit-identical); slot j
+// is the j-th smallest of the K winners.  Block 0 publishes idx/w.
+// Up to gating::kCountMaxE experts the steps are written out for one key per
+// lane: this runs in front of every workgroup's weight stream (Mixtral shapes:
+// 3.5 rounds of workgroups, gate/up 71.2 us so and 72.4 through route_row).
+__device__ __forceinline__ int b1_routed_few(const FfnArgs& a, const float* zp, int j, float& wj, int& n_routed) {
+    const int E = a.E, K = a.K, lane = threadIdx.x & 63;
+    const float z = lane < E ? zp[lane] : 0.f;
+    const uint32_t key = lane < E ? gating::order_key(z) : 0u;
+    int pos = 0;                                   // keys that beat this lane's
+#pragma unroll 8
+    for (int g = 0; g < E; ++g) {
+        const uint32_t kg = uint32_t(lane_i(int(key), g));
+        pos += kg > key || (kg == key && g < lane);
+    }
+    const bool win = lane < E && pos < K;
+    unsigned long long W = __ballot(win);
+    // the row max is the logit of the position-0 winner
+    const float m = lane_f(z, __ffsll(__ballot(win && pos == 0)) - 1);
+    const float s = wave_sum(lane < E ? expf(z - m) : 0.f);
+    // lane k < K: expert and probability of the position-k winner
+    int ek = 0;
+    for (int k = 0; k < K; ++k) {
+        const int f = __ffsll(__ballot(win && pos == k)) - 1;
+        if (lane == k) ek = f;
+    }
+    const float zk = __shfl(z, ek, 64);
+    float p = 0.f;
+    if (lane < K) p = expf(zk - m) / s;
+    const float wsum = wave_sum(p);
+    const float wt = a.renorm ? p / wsum : p;
+    if (blockIdx.x == 0 && threadIdx.x < K) {
+        const_cast<int32_t*>(a.idx)[lane] = ek;
+        const_cast<float*>(a.w)[lane] = wt;
+    }
+    n_routed = K;
+    if (j >= K) return -1;
+    for (int q = 0; q < j; ++q) W &= W - 1ull;     // the j-th winner by index
+    const int e = __ffsll(W) - 1;
+    wj = lane_f(wt, lane_i(pos, e));
+    return e;
+}
+
 __device__ __forceinline__ int b1_routed(const FfnArgs& a, const float* z, int j, float& wj, int& n_routed,
                                          int32_t* sel, float* prob) {
     const int K = a.K, lane = threadIdx.x & 63;
+    if (a.E <= gating::kCountMaxE) return b1_routed_few(a, z, j, wj, n_routed);
     int ek;
     float wk;
     gating::route_row(z, a.E, K, a.renorm, sel, prob, ek, wk);
@@ -487,8 +529,7 @@ __device__ __forceinline__ int b1_routed(const FfnArgs& a, const float* z, int j
     n_routed = K;
     if (j >= K) return -1;
     int place = 0;
-#pragma unroll
-    for (int r = 0; r < kMaxK; ++r) place += r < K && lane_i(ek, r) < ek;
+    for (int r = 0; r < K; ++r) place += lane_i(ek, r) < ek;
     const int src = __ffsll(__ballot(lane < K && place == j)) - 1;
     wj = lane_f(wk, src);
     return lane_i(ek, src);

@@ -120,124 +120,145 @@ __device__ void expert_logits(const RouteArgs& a, float (*part)[kThreads / 64]) 
     }
 }
 
+constexpr int kKeyRegs = kMaxE / 64;   // keys per lane of a wave that holds a row
 constexpr int kCountMaxE = 32;
 
-// Softmax and top-K of one batch row by one wave, in registers: lane l holds
-// the logits l, l + 64, ... (E <= 256).  Up to kCountMaxE experts each counts
-// the ones that beat it; beyond, the K-th largest order key is found
-// bit by bit, the largest first: a ballot counts the experts whose key reaches
-// the candidate, and the search ends as soon as exactly K do (always for
-// distinct keys; equal keys that straddle the K-th place are taken at the
-// lower expert indices).  The winners then count each other for their
-// positions (logit desc, index asc).  The router tail and the expert FFN's
-// routing prologue both run this, so their selections and weights are
-// bit-identical.  Each wave works alone: no barrier.
-//
-// z [E] (global or LDS); sel [K], prob [K]: this row's, in LDS.  Lanes k < K
-// return the expert and weight of position k; sel/prob hold them as well.
-// Weights assume NaN-free logits (NaN ranks below every number).
-__device__ __forceinline__ void route_row(const float* z, int E, int K, int renorm, int32_t* sel, float* prob, int& e,
-                                          float& wt) {
-    constexpr int V = kMaxE / 64;
+// The K largest of a row of E <= 256 keys, by one wave in registers: lane l
+// holds the keys of l, l + 64, ... (0 where `ok` is false).  Marks the winners
+// and their positions (key desc, index asc).  Up to kCountMaxE keys each
+// counts the ones that beat it; beyond, the K-th largest key is found bit by
+// bit, the largest first: a ballot counts the keys that reach the candidate,
+// and the search ends as soon as exactly K do (always for distinct keys; equal
+// keys that straddle the K-th place are taken at the lower indices); the
+// winners then count each other.
+__device__ __forceinline__ void topk_positions(const uint32_t (&key)[kKeyRegs], const bool (&ok)[kKeyRegs], int E, int K,
+                                               bool (&win)[kKeyRegs], int (&pos)[kKeyRegs]) {
+    constexpr int V = kKeyRegs;
     const int lane = threadIdx.x & 63;
-    float zv[V];
-    uint32_t key[V];
-    bool ok[V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int f = 64 * v + lane;
-        ok[v] = f < E;
-        zv[v] = ok[v] ? z[f] : 0.f;
-    }
-#pragma unroll
-    for (int v = 0; v < V; ++v) key[v] = ok[v] ? order_key(zv[v]) : 0u;
-    bool win[V];
-    int pos[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         win[v] = false;
         pos[v] = 0;
     }
     if (E <= kCountMaxE) {
-        // few experts: each counts all that beat it (its position)
 #pragma unroll 8
         for (int g = 0; g < E; ++g) {
             const uint32_t kg = uint32_t(__builtin_amdgcn_readlane(int(key[0]), g));
             pos[0] += kg > key[0] || (kg == key[0] && g < lane);
         }
         win[0] = ok[0] && pos[0] < K;
+        return;
+    }
+    // p: the largest value that at least K keys reach
+    uint32_t p = 0u;
+    int reach = E;
+    for (int bit = 31; bit >= 0 && reach != K; --bit) {
+        const uint32_t cand = p | (1u << bit);
+        int n = 0;
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (64 * v < E) n += __popcll(__ballot(key[v] >= cand));   // a padding key (0) reaches no candidate
+        if (n >= K) {
+            p = cand;
+            reach = n;
+        }
+    }
+    if (reach == K) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) win[v] = ok[v] && key[v] >= p;
     } else {
-        // p: the largest value that at least K keys reach
-        uint32_t p = 0u;
-        int reach = E;
-        for (int bit = 31; bit >= 0 && reach != K; --bit) {
-            const uint32_t cand = p | (1u << bit);
-            int n = 0;
+        // more than K keys reach p, the K-th largest: keys above it win, then equal ones by index
+        int above = 0, tied = 0;
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (64 * v < E) n += __popcll(__ballot(key[v] >= cand));   // a padding key (0) reaches no candidate
-            if (n >= K) {
-                p = cand;
-                reach = n;
-            }
-        }
-        if (reach == K) {
-#pragma unroll
-            for (int v = 0; v < V; ++v) win[v] = ok[v] && key[v] >= p;
-        } else {
-            // more than K keys reach p, the K-th largest: keys above it win, then equal ones by index
-            int above = 0, tied = 0;
-#pragma unroll
-            for (int v = 0; v < V; ++v) above += __popcll(__ballot(ok[v] && key[v] > p));
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const bool tie = ok[v] && key[v] == p;
-                const unsigned long long tm = __ballot(tie);
-                win[v] = ok[v] && (key[v] > p || (tie && above + tied + __popcll(tm & ((1ull << lane) - 1ull)) < K));
-                tied += __popcll(tm);
-            }
-        }
+        for (int v = 0; v < V; ++v) above += __popcll(__ballot(ok[v] && key[v] > p));
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            unsigned long long m = __ballot(win[v]);
-            while (m) {
-                const int l = __ffsll(m) - 1, g = 64 * v + l;
-                m &= m - 1ull;
-                const uint32_t kg = uint32_t(__builtin_amdgcn_readlane(int(key[v]), l));
+            const bool tie = ok[v] && key[v] == p;
+            const unsigned long long tm = __ballot(tie);
+            win[v] = ok[v] && (key[v] > p || (tie && above + tied + __popcll(tm & ((1ull << lane) - 1ull)) < K));
+            tied += __popcll(tm);
+        }
+    }
 #pragma unroll
-                for (int u = 0; u < V; ++u)
-                    if (64 * u < E) pos[u] += kg > key[u] || (kg == key[u] && g < 64 * u + lane);
+    for (int v = 0; v < V; ++v) {
+        unsigned long long m = __ballot(win[v]);
+        while (m) {
+            const int l = __ffsll(m) - 1, g = 64 * v + l;
+            m &= m - 1ull;
+            const uint32_t kg = uint32_t(__builtin_amdgcn_readlane(int(key[v]), l));
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if (64 * u < E) pos[u] += kg > key[u] || (kg == key[u] && g < 64 * u + lane);
+        }
+    }
+}
+
+// Softmax and top-K of one batch row by one wave, in registers.  The router
+// tail and the expert FFN's routing prologue both run this, so their
+// selections and weights are bit-identical.  Each wave works alone: no barrier.
+//
+// z [E] (global or LDS); sel [K], prob [K]: this row's, in LDS.  Lanes k < K
+// return the expert and weight of position k; sel/prob hold them as well.
+// Weights assume NaN-free logits (NaN ranks below every number).
+__device__ __forceinline__ void route_row(const float* z, int E, int K, int renorm, int32_t* sel, float* prob, int& e,
+                                          float& wt) {
+    constexpr int V = kKeyRegs;
+    const int lane = threadIdx.x & 63;
+    float zv[V];
+    uint32_t key[V];
+    bool ok[V], win[V];
+    int pos[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int f = 64 * v + lane;
+        ok[v] = f < E;
+        zv[v] = 64 * v < E ? z[min(f, E - 1)] : 0.f;      // no branch per lane: the loads issue together
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) key[v] = 64 * v < E && ok[v] ? order_key(zv[v]) : 0u;
+    topk_positions(key, ok, E, K, win, pos);
+    // lane k: expert and logit of position k
+    float zk = 0.f;
+    e = 0;
+    if (E <= 64 && K <= 8) {
+        // few positions: ballots, no LDS round trip in front of the weights
+        for (int k = 0; k < K; ++k) {
+            const int src = __ffsll(__ballot(win[0] && pos[0] == k)) - 1;
+            const float zs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zv[0]), src));
+            if (lane == k) {
+                e = src;
+                zk = zs;
             }
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (win[v]) {
+                sel[pos[v]] = 64 * v + lane;
+                prob[pos[v]] = zv[v];
+            }
+        // a wave's LDS accesses complete in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (lane < K) {
+            e = sel[lane];
+            zk = prob[lane];
         }
     }
     // the row max is the logit of the position-0 winner
-    float m = 0.f;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const unsigned long long t = __ballot(win[v] && pos[v] == 0);
-        if (t) m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zv[v]), __ffsll(t) - 1));
-        if (win[v]) {
-            sel[pos[v]] = 64 * v + lane;
-            prob[pos[v]] = zv[v];
-        }
-    }
+    const float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zk), 0));
     float s = 0.f;
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (ok[v]) s += expf(zv[v] - m);
+        if (64 * v < E && ok[v]) s += expf(zv[v] - m);
     s = wave_sum(s);
-    // a wave's LDS accesses complete in order: position k's expert and logit
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    float pk = 0.f;
-    e = 0;
-    if (lane < K) {
-        e = sel[lane];
-        pk = expf(prob[lane] - m) / s;
-    }
+    const float pk = lane < K ? expf(zk - m) / s : 0.f;
     const float wsum = wave_sum(pk);
     wt = renorm ? pk / wsum : pk;
-    if (lane < K) prob[lane] = wt;
+    if (lane < K) {
+        sel[lane] = e;
+        prob[lane] = wt;
+    }
 }
 
 // The router tail, one wave per batch row: writes idx/w (and leaves the
