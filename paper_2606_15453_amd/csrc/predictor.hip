@@ -24,36 +24,56 @@ using namespace pred;
 constexpr int kThreads = 256;    // of the profiling kernels and the decode path's
 
 // ---------------------------------------------------------------- profiling
-// Algorithm 1, counting: one workgroup per (profiling token, layer pair).
-__global__ __launch_bounds__(kThreads) void co_count_kernel(const int32_t* sel, int P, int B, int L,
-                                                            int E, int K, int32_t* co) {
-    const int p = blockIdx.x, i = blockIdx.y;
-    const int pairs = B * K * K;
-    for (int t = threadIdx.x; t < pairs; t += kThreads) {
-        const int b = t / (K * K), r = (t / K) % K, s = t % K;
-        const int32_t* row = sel + ((size_t(p) * B + b) * L) * K;
-        const int e = row[i * K + r], f = row[(i + 1) * K + s];
-        atomicAdd(&co[(size_t(i) * E + e) * E + f], 1);
-    }
-}
+constexpr int kCountThreads = 1024;
+constexpr int kCountSlice = 8192;     // counts a workgroup holds in LDS
 
-// Algorithm 1, selection: CCT_i[e] = the K largest counts of Co_i[e][*]
-// (equal counts -> lower index), all with confidence "10".
-__global__ __launch_bounds__(kThreads) void cct_build_kernel(const int32_t* co, int E, int K,
-                                                             size_t stride, uint8_t* idx, uint8_t* conf) {
-    __shared__ int32_t row[kMaxE];
-    const size_t r = blockIdx.x;   // (pair, expert) row
-    const size_t out = (r / E) * stride + (r % E) * K;
-    for (int f = threadIdx.x; f < E; f += kThreads) row[f] = co[r * E + f];
+// Rows of Co_i one workgroup counts: as many as fit its LDS counts.
+inline int count_rows(int E) { return std::min(E, kCountSlice / E); }
+
+// Algorithm 1: one workgroup counts `rows` rows of Co_i (blockIdx.y = i) over a
+// chunk of n profiling tokens, in LDS, and after the last chunk selects
+// CCT_i[e] from them: the K largest counts of Co_i[e][*] (equal counts ->
+// lower index), all with confidence "10", one wave per row.  Counting into
+// global memory with an atomic per pair took 45 us (48 layers of 128 experts,
+// 512 rows of top-8), clearing it 6 and a selection launch 17.5; this takes
+// the place of all three.
+__global__ __launch_bounds__(kCountThreads) void co_build_kernel(const int32_t* sel, int n, int B, int L, int E, int K,
+                                                                 int rows, int first, int last, int32_t* co,
+                                                                 size_t stride, uint8_t* idx, uint8_t* conf) {
+    __shared__ int32_t cnt[kCountSlice];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = blockIdx.y;
+    const int e0 = blockIdx.x * rows, nr = min(rows, E - e0);
+    int32_t* out = co + (size_t(i) * E + e0) * E;
+    for (int t = tid; t < nr * E; t += kCountThreads) cnt[t] = first ? 0 : out[t];
     __syncthreads();
-    for (int f = threadIdx.x; f < E; f += kThreads) {
-        const int32_t c = row[f];
-        int rank = 0;
-        for (int g = 0; g < E; ++g) rank += (row[g] > c) || (row[g] == c && g < f);
-        if (rank < K) {
-            idx[out + rank] = uint8_t(f);
-            conf[out + rank] = uint8_t(kConfInit);
+    for (int t = tid; t < n * B * K; t += kCountThreads) {
+        const int pb = t / K;
+        const int32_t* row = sel + (size_t(pb) * L + i) * K;
+        const int e = row[t - pb * K] - e0;
+        if (e < 0 || e >= nr) continue;
+        for (int s = 0; s < K; ++s) atomicAdd(&cnt[e * E + row[K + s]], 1);
+    }
+    __syncthreads();
+    for (int t = tid; t < nr * E; t += kCountThreads) out[t] = cnt[t];
+    if (!last) return;
+    for (int r = wave; r < nr; r += kCountThreads / 64) {
+        uint32_t key[gating::kKeyRegs];
+        bool ok[gating::kKeyRegs], win[gating::kKeyRegs];
+        int pos[gating::kKeyRegs];
+#pragma unroll
+        for (int v = 0; v < gating::kKeyRegs; ++v) {
+            const int f = 64 * v + lane;
+            ok[v] = f < E;
+            key[v] = ok[v] ? uint32_t(cnt[r * E + f]) : 0u;
         }
+        gating::topk_positions(key, ok, E, K, win, pos);
+        const size_t at = size_t(i) * stride + size_t(e0 + r) * K;
+#pragma unroll
+        for (int v = 0; v < gating::kKeyRegs; ++v)
+            if (win[v]) {
+                idx[at + pos[v]] = uint8_t(64 * v + lane);
+                conf[at + pos[v]] = uint8_t(kConfInit);
+            }
     }
 }
 
@@ -293,26 +313,21 @@ extern "C" int stmoe_profile(stmoe_predictor* p, const int32_t* sel, int P) {
     if (int rc = check_sel_host(sel, size_t(P) * B * L, E, K)) return rc;
     const size_t tok = size_t(B) * L * K;                 // int32 per profiling token
     const int chunk = int(p->stage_bytes / (tok * sizeof(int32_t)));
-    const size_t pairs = size_t(L > 1 ? L - 1 : 1);
+    const int rows = count_rows(E);
     // the legacy null stream orders the blocking copies and the kernels
-    hipError_t e = hipMemset(p->co, 0, pairs * E * E * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(p->pend, 0, size_t(L) * p->pend_stride);
+    hipError_t e = hipMemset(p->pend, 0, size_t(L) * p->pend_stride);
     if (e == hipSuccess) e = hipMemset(p->stats, 0, size_t(L) * 3 * sizeof(unsigned long long));
     int last_at = 0;
     for (int t0 = 0; t0 < P && e == hipSuccess; t0 += chunk) {
         const int n = std::min(chunk, P - t0);
         e = hipMemcpy(p->stage, sel + size_t(t0) * tok, size_t(n) * tok * sizeof(int32_t), hipMemcpyHostToDevice);
         if (e == hipSuccess && L > 1) {
-            hipLaunchKernelGGL(co_count_kernel, dim3(n, L - 1), dim3(kThreads), 0, 0, p->stage, n, B, L, E, K,
-                               p->co);
+            hipLaunchKernelGGL(co_build_kernel, dim3(unsigned((E + rows - 1) / rows), unsigned(L - 1)),
+                               dim3(kCountThreads), 0, 0, p->stage, n, B, L, E, K, rows, t0 == 0, t0 + n == P, p->co,
+                               p->cct_stride, p->cct_idx, p->cct_conf);
             e = hipGetLastError();
         }
         last_at = P - 1 - t0;                             // the last token's row within the final chunk
-    }
-    if (e == hipSuccess && L > 1) {
-        hipLaunchKernelGGL(cct_build_kernel, dim3(unsigned((L - 1) * E)), dim3(kThreads), 0, 0,
-                           p->co, E, K, p->cct_stride, p->cct_idx, p->cct_conf);
-        e = hipGetLastError();
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(ht_init_kernel, dim3(L, B), dim3(kThreads), 0, 0, p->stage + size_t(last_at) * tok,
