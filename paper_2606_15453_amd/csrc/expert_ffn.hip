@@ -1646,12 +1646,12 @@ void launch_up_tile(const FfnArgs& a, hipStream_t st) {
     // split the columns over the waves where each wave keeps two steps of them
     // (DeepSeek-V2-Lite shapes at batch 4: 43.2 us split, 47.6 not; rows of
     // 1408 bytes at batch 14, gate/up + down: 49.5 against 36.2)
-    // With four token groups a split tile's share is worth its prologue only
-    // where the plan is ready and rows are long (gate/up + down: Qwen3-235B
-    // shapes, batch 16, 460 us against 472, without the plan 496 against 464;
-    // Qwen3-30B shapes, batch 16, 134 against 127).
-    const int rowb = a.H * (BF ? 2 : 4);
-    const bool sk = TG < 4 ? rowb >= 2 * kWaves * 256 : a.ready && rowb >= 8 * kWaves * 256;
+    // With four token groups a split tile's share is not worth its prologue
+    // (gate/up + down: Qwen3-30B shapes, batch 16, 134 us split with the plan
+    // ready, 163 without, 127 not split; Qwen3-235B shapes 460, 496, 466).  The
+    // rule must not ask for the plan: the same layer runs with and without one
+    // (resident and cached) and gives the same bits.
+    const bool sk = TG < 4 && a.H * (BF ? 2 : 4) >= 2 * kWaves * 256;
     const int rows = sk ? 4 : 4 * kWaves, bps = (a.I + rows - 1) / rows;
     const dim3 grid(unsigned(bps * a.cap + extra));
     if (sk) hipLaunchKernelGGL((ffn_up_tile<BF, TG, true>), grid, dim3(kThreads), 0, st, a, bps);
