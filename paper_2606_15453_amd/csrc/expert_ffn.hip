@@ -19,7 +19,8 @@
 //            the L2 of every XCD), and the summation order depends only on the
 //            routing, never on where the blobs live.
 //
-// Batch 1, and bf16 shapes whose activations are held in fp32: GEMV kernels.
+// Batch 1, bf16 shapes whose activations are held in fp32, and some small
+// shapes of batch 2 to 4 (plan_shape): GEMV kernels.
 // A group of G lanes (64, 32 or 16, by row length) owns R rows and strides
 // over their 16-byte chunks; the activations come from L1/L2; DPP / shuffle
 // segment sums reduce.  For long down rows the whole workgroup strides one
@@ -1508,7 +1509,16 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // (three bf16 operands per activation on the matrix cores summed to 5.0e-7
     // of the 64-bit result, the GEMV to 3.1e-7).
     const bool act16 = dtype == STMOE_BF16 && ((B == 8 && H % 64 == 0 && I % 64 == 0) || act_bf16<true>(s, B));
-    s.tile = B >= 2 && !s.mfma && (dtype == STMOE_F32 || act16);
+    // Two tokens, or up to four with fp32 weights and few long rows, keep the
+    // GEMV kernels where their lane groups have no idle lanes and the tiles'
+    // down grid has at most one workgroup per CU: E 32 H 1024 I 704 at batch 2
+    // bf16 13.9 us against 14.6, fp32 17.6 against 18.2; E 8 H 768 I 3072 at
+    // batch 2 16.1 against 17.1, fp32 24.6 against 26.5, at batch 3 30.8
+    // against 32.3 (bf16 there 20.9 against 19.6).  Beyond: E 16 H 2048 I 1024
+    // at batch 2 15.8 against 15.4; E 60 H 520 I 264 11.9 against 10.2; E 32
+    // H 1024 I 704 at batch 3 fp32 24.4 against 22.9.
+    const bool few = H <= 1024 && H % 128 == 0 && (B == 2 || (dtype == STMOE_F32 && B <= 4 && I >= 2 * H));
+    s.tile = B >= 2 && !s.mfma && !few && (dtype == STMOE_F32 || act16);
     if (s.tile) {
         s.dn_kind = 3;
         return s;
@@ -1577,7 +1587,7 @@ int launch_gate_up(const FfnArgs& a, const Shape& s, hipStream_t st) {
 template <bool BF, int NB, int U>
 void launch_down_rows_u(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const dim3 grid(unsigned(s.n_rb));
-    if constexpr (NB > 1) {      // four rows per group, or the shape takes 4-row tiles
+    if constexpr (NB > 4) {      // four rows per group, or the shape takes 4-row tiles
         hipLaunchKernelGGL((ffn_down_rows<BF, 64, 4, NB, U>), grid, dim3(kThreads), 0, st, a);
         return;
     }
@@ -1629,12 +1639,12 @@ int launch_gemv(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_
 
 template <bool BF>
 int launch_gemv_b(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
-    if constexpr (BF) {      // fp32 weights run on tiles from batch 2
+    if constexpr (BF) {      // fp32 weights always run on tiles from batch 5
         if (a.B > 8) return launch_gemv<BF, 16>(a, s, st, ev_mid);
         if (a.B > 4) return launch_gemv<BF, 8>(a, s, st, ev_mid);
-        if (a.B > 2) return launch_gemv<BF, 4>(a, s, st, ev_mid);
-        if (a.B > 1) return launch_gemv<BF, 2>(a, s, st, ev_mid);
     }
+    if (a.B > 2) return launch_gemv<BF, 4>(a, s, st, ev_mid);
+    if (a.B > 1) return launch_gemv<BF, 2>(a, s, st, ev_mid);
     return launch_gemv<BF, 1>(a, s, st, ev_mid);
 }
 
@@ -1658,13 +1668,13 @@ void launch_up_tile(const FfnArgs& a, hipStream_t st) {
     else hipLaunchKernelGGL((ffn_up_tile<BF, TG, false>), grid, dim3(kThreads), 0, st, a, bps);
 }
 
-template <bool BF, int RQ, int TG>
+template <bool BF, int RQ, int TG, int W>
 void launch_down_tile_r(const FfnArgs& a, hipStream_t st) {
-    const dim3 grid(unsigned(a.H / (4 * RQ))), block(64 * kDownWaves);
+    const dim3 grid(unsigned(a.H / (4 * RQ))), block(64 * W);
     if (a.I * (BF ? 2 : 4) % 256)
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true>), grid, block, 0, st, a);
     else
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, false>), grid, block, 0, st, a);
 }
 
 template <bool BF, int TG>
@@ -1674,8 +1684,18 @@ void launch_down_tile(const FfnArgs& a, hipStream_t st) {
     // fp32, batch 8: 15.9 against 23.1).  One workgroup of the former fills a
     // CU: compare the rows of the busiest CU, a row at about 9/8 in the latter.
     const int rows2 = (a.H / 8 + 255) / 256 * 8, rows1 = (a.H / 4 + 255) / 256 * 4;
-    if (8 * rows2 <= 9 * rows1) launch_down_tile_r<BF, 2, TG>(a, st);
-    else launch_down_tile_r<BF, 1, TG>(a, st);
+    if (8 * rows2 <= 9 * rows1) {
+        launch_down_tile_r<BF, 2, TG, 8>(a, st);
+        return;
+    }
+    // at most one workgroup per CU: sixteen waves, for the bytes in flight
+    if constexpr (TG < 4) {
+        if (a.H <= 1024) {
+            launch_down_tile_r<BF, 1, TG, 16>(a, st);
+            return;
+        }
+    }
+    launch_down_tile_r<BF, 1, TG, 8>(a, st);
 }
 
 template <bool BF, int TG>

@@ -479,16 +479,14 @@ __global__ __launch_bounds__(kThreads, TG == 4 ? 4 : TG == 2 ? 6 : 7) void ffn_u
     else up_stream<BF, 1, TG, kUpTileSteps, SK>(a, z, mytok, myw, red);
 }
 
-constexpr int kDownWaves = 8;          // waves of a down workgroup
-constexpr int kDownTileSteps = 3;      // steps in flight per wave (down)
-
 // down: one workgroup = 4 * RQ output rows; its waves split the (slot, step)
-// pairs of all slots evenly and stream them without a break at a slot's end.
+// pairs of all slots evenly and stream them without a break at a slot's end, U
+// steps in flight per wave.
 // Workgroups start one step apart and run around the pairs (rows a power of
 // two apart read different memory channels).
-template <bool BF, int RQ, int TG, bool REM>
-__global__ __launch_bounds__(64 * kDownWaves, (TG == 4 ? 2 : TG * RQ == 4 ? 3 : 4)) void ffn_down_tile(FfnArgs a) {
-    constexpr int W = kDownWaves, U = kDownTileSteps;
+template <bool BF, int RQ, int TG, int W, bool REM>
+__global__ __launch_bounds__(64 * W, (W == 16 ? 4 : TG == 4 ? 2 : TG * RQ == 4 ? 3 : 4)) void ffn_down_tile(FfnArgs a) {
+    constexpr int U = W == 16 && TG == 1 ? 4 : 3;
     __shared__ SlotTable p;
     __shared__ float red[W][RQ][TG][16];
     const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
