@@ -135,7 +135,7 @@ def parse():
 COUNTERS_MD = os.path.join(ROOT, "profiles", "ffn_gate_up_mixtral8x7b_b1_counters.md")
 POOL_TIER = "host"      # set from --pool
 FFN_SOURCES = [os.path.join(ROOT, "paper_2606_15453_amd", "csrc", f)
-               for f in ("expert_ffn.hip", "gating_dev.h", "common.h")]
+               for f in ("expert_ffn.hip", "ffn_tile.h", "gating_dev.h", "common.h")]
 CALIB_BYTES = 1 << 30
 COUNTER_TOKENS = 20
 
@@ -659,7 +659,7 @@ def ffn_sweep(calls=60, cold_bytes=2 << 30):
         us = e0.elapsed_time(e1) * 1e3 / calls
         nbytes = nb * cfg.blob_bytes
         gbps = nbytes / us / 1e3
-        path = "MFMA" if (cfg.B >= 8 and cfg.dtype == "bf16") else "GEMV"
+        path = "MFMA" if cfg.B >= 8 or (cfg.B >= 2 and cfg.H < 4096) else "GEMV"
         print(f"| {cfg.name} | {cfg.B} | {len(sel)} (+{cfg.n_shared}) | {nbytes} | {n_sets} | {us:.1f} | {gbps:.0f} | "
               f"{gbps / PEAK_HBM_GBPS:.3f} | {path} |", flush=True)
         del store

@@ -201,9 +201,10 @@ int moe_pack_expert(const void* w_gate, const void* w_up, const void* w_down, in
  *                256-byte aligned (activations and partial sums; no initial
  *                contents required); calls sharing it must be ordered on one
  *                stream
- *   B < 8 runs the GEMV kernels; B >= 8 with bf16 and H, I multiples of 64
- *   runs the MFMA grouped-GEMM kernels (the SwiGLU activation then passes
- *   through bf16); other shapes fall back to the GEMV kernels.
+ *   B 1, bf16 shapes whose activations are held in fp32 and some small shapes
+ *   run GEMV kernels, B 2 to 8 (and fp32 or ragged sizes beyond) 4-row MFMA
+ *   tiles, larger B 16-row MFMA tiles; on the tiles the SwiGLU activation of
+ *   bf16 weights passes through bf16.
  * ---------------------------------------------------------------------- */
 size_t moe_expert_ffn_workspace_bytes(int B, int K, int E, int H, int I, int n_shared, int dtype);
 int moe_expert_ffn(const void* x, const int32_t* topk_idx, const float* topk_w, int B, int K,
