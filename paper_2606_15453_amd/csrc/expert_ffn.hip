@@ -39,9 +39,9 @@
 // it runs (ffn_route_plan): a gate/up workgroup then reads one record, where
 // building the plan in LDS costs each round of workgroups about 2 us
 // (Qwen3-30B shapes at batch 8: 3072 workgroups in four rounds).  Otherwise
-// every gate/up workgroup rebuilds it from topk_idx/topk_w, with no host
-// round trip or planning launch, and one leaves it to the down launch; the
-// GEMV kernels rebuild it in both.
+// every 4-row gate/up workgroup rebuilds it from topk_idx/topk_w, with no host
+// round trip or planning launch, and one that does nothing else leaves it to
+// the down launch; the GEMV and the 16-row kernels rebuild it in both.
 #include <mutex>
 #include <type_traits>
 
@@ -924,30 +924,17 @@ __global__ __launch_bounds__(kThreads) void ffn_down_wg(FfnArgs a) {
 }
 
 // ============================================================================
-// MFMA path (batch >= 8, bf16, H and I multiples of 64)
+// 16-row MFMA path (batch > 8, bf16, H and I multiples of 64)
 // ============================================================================
 
-// Slot j of a gate/up workgroup: from the plan made beforehand, or built here
-// (workgroup 0 then publishes it for the down launch).  False: no such slot.
-__device__ bool mfma_slot(const FfnArgs& a, Plan& p, int j, const char*& blob, unsigned& tm) {
-    if (a.ready) {
-        const SlotRec& r = a.slots->rec[j];
-        blob = r.blob;
-        tm = r.tok;
-        return r.nt != 0;
-    }
-    build_plan(a, p, true);
-    if (blockIdx.x == 0) publish_plan<kThreads>(a, p.idx, p.w);
-    if (j >= p.n_slots) return false;
-    blob = slot_blob(a, p, j);
-    tm = p.tok[j];
-    return true;
-}
-
-// Gate weight of token b, which the slot serves.
-__device__ __forceinline__ float mfma_weight(const FfnArgs& a, const Plan& p, int j, unsigned tm, int b) {
-    return a.ready ? a.slots->rec[j].w[__popc(tm & ((1u << b) - 1u))] : slot_weight(a, p, j, b);
-}
+// The slots of a 16-row down workgroup: from the list that a gate/up launch on
+// 4-row tiles goes with (LIST), else rebuilt from the selection.  Reading the
+// list behind a 16-row gate/up launch, whose first workgroup would publish it
+// before its own weights, cost 2.5 to 4 us a call (H 1024 I 1024 E 32 top-8:
+// batch 16 50.4 us against 48.0; DeepSeek-V2-Lite shapes, batch 12: 125.8
+// against 121.6).
+template <bool LIST>
+using MfmaDownPlan = typename std::conditional<LIST, SlotTable, PlanB>::type;
 
 // gate/up: each wave computes NT tiles of 16 rows x 16 tokens for W_gate and
 // W_up over the whole hidden dimension, then writes the bf16 activation
@@ -955,10 +942,11 @@ __device__ __forceinline__ float mfma_weight(const FfnArgs& a, const Plan& p, in
 template <int NT>
 __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma(FfnArgs a, int blocks_per_slot) {
     __shared__ Plan p;
+    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    const char* blob;
-    unsigned tm;
-    if (!mfma_slot(a, p, j, blob, tm)) return;
+    if (j >= p.n_slots) return;
+    const unsigned tm = p.tok[j];
+    const char* blob = slot_blob(a, p, j);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = (blockIdx.x % blocks_per_slot) * (kWaves * NT * 16) + wave * NT * 16;
@@ -1030,7 +1018,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma(FfnArgs a, int bloc
         const int b = 4 * q + r;
         if (b >= a.B) continue;
         const bool routed = (tm >> b) & 1u;
-        const float wb = routed ? mfma_weight(a, p, j, tm, b) : 0.f;
+        const float wb = routed ? slot_weight(a, p, j, b) : 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = routed ? wb * silu(dg[t][r]) * du[t][r] : 0.f;
@@ -1059,10 +1047,11 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
     __shared__ Plan p;
     __shared__ float red[SK ? kWaves : 1][2][64][4];
     extern __shared__ uint4 stage[];
+    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    const char* blob;
-    unsigned tm;
-    if (!mfma_slot(a, p, j, blob, tm)) return;
+    if (j >= p.n_slots) return;
+    const unsigned tm = p.tok[j];
+    const char* blob = slot_blob(a, p, j);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = SK ? (blockIdx.x % blocks_per_slot) * 16
@@ -1155,7 +1144,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
         const int b = 4 * q + r;
         if (b >= a.B) continue;
         const bool routed = (tm >> b) & 1u;
-        const float wb = routed ? mfma_weight(a, p, j, tm, b) : 0.f;
+        const float wb = routed ? slot_weight(a, p, j, b) : 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = routed ? wb * silu(dg[t][r]) * du[t][r] : 0.f;
@@ -1167,11 +1156,11 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_lds(FfnArgs a, int 
 // down through LDS: as the gate/up kernel, with W_down rows (length I) as the
 // staged operand and the slot's bf16 activations as the A operand, summing
 // the slots of the workgroup's group.
-template <int NT>
+template <int NT, bool LIST>
 __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
-    __shared__ SlotTable p;
+    __shared__ MfmaDownPlan<LIST> p;
     extern __shared__ uint4 stage[];
-    load_slots(a, p);
+    down_plan(a, p);
     const int rb = blockIdx.x / a.ng, grp = blockIdx.x % a.ng;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
@@ -1200,10 +1189,10 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
     const int total = live ? (j1 - j0) * steps : 0;
     uint4 ld[kLoads];
     bf16x8 av[4], an[4];
-    // only routed tokens' activations exist: the other rows are zero operands
-    bool rt = false, rn = false;
+    // LIST: only routed tokens' activations exist, the other rows are zero operands
+    bool rt = arow, rn = arow;
     auto issue = [&](int j, int k, bf16x8 (&ax)[4], bool& routed) {
-        routed = (p.tok[j] >> n) & 1u;
+        if constexpr (LIST) routed = (p.tok[j] >> n) & 1u;
         const char* wd = p.blob[j] + 2 * size_t(a.I) * a.H * 2 + size_t(k) * 2;
         const char* ar = reinterpret_cast<const char*>(a.act) + (size_t(j) * a.B + (arow ? n : 0)) * rowb +
                          q * 16 + size_t(k) * 2;
@@ -1261,10 +1250,11 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma_lds(FfnArgs a) {
 __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_sk(FfnArgs a, int blocks_per_slot) {
     __shared__ Plan p;
     __shared__ float red[kWaves][2][64][4];
+    build_plan(a, p, true);
     const int j = blockIdx.x / blocks_per_slot;
-    const char* blob;
-    unsigned tm;
-    if (!mfma_slot(a, p, j, blob, tm)) return;
+    if (j >= p.n_slots) return;
+    const unsigned tm = p.tok[j];
+    const char* blob = slot_blob(a, p, j);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int i0 = (blockIdx.x % blocks_per_slot) * 16;   // I is a multiple of 16
@@ -1318,17 +1308,17 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_mfma_sk(FfnArgs a, int b
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) { g += red[w][0][lane][r]; u += red[w][1][lane][r]; }
         const bool routed = (tm >> b) & 1u;
-        const float v = routed ? mfma_weight(a, p, j, tm, b) * silu(g) * u : 0.f;
+        const float v = routed ? slot_weight(a, p, j, b) * silu(g) * u : 0.f;
         act[size_t(b) * a.I + i0 + n] = f32_to_bf16_rne(v);
     }
 }
 
 // down: each wave computes NT tiles of 16 output rows x 16 tokens, summing
 // the slots of its group (A operand = the slot's bf16 activations).
-template <int NT>
+template <int NT, bool LIST>
 __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
-    __shared__ SlotTable p;
-    load_slots(a, p);
+    __shared__ MfmaDownPlan<LIST> p;
+    down_plan(a, p);
     const int rb = blockIdx.x / a.ng, grp = blockIdx.x % a.ng;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
@@ -1350,7 +1340,7 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
         const char* wr[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) wr[t] = wd + size_t(h0 + t * 16 + n) * rowb;
-        const bool rt = (p.tok[j] >> n) & 1u;      // only routed tokens' activations exist
+        const bool rt = LIST ? (p.tok[j] >> n) & 1u : arow;      // LIST: only routed tokens' activations exist
         const char* ar = reinterpret_cast<const char*>(a.act) +
                          (size_t(j) * a.B + (arow ? n : 0)) * rowb + q * 16;
         auto step = [&](const bf16x8 (&w0)[NT], const bf16x8 (&w1)[NT], const bf16x8& a0, const bf16x8& a1) {
@@ -1715,6 +1705,17 @@ int launch_tile(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
     return launch_tile_t<BF, 4>(a, st, ev_mid);
 }
 
+template <bool LIST>
+void launch_down_mfma(const FfnArgs& a, int nt, bool lds, dim3 grid, unsigned bytes, hipStream_t st) {
+    if (nt == 2) {
+        if (lds) hipLaunchKernelGGL((ffn_down_mfma_lds<2, LIST>), grid, dim3(kThreads), bytes, st, a);
+        else hipLaunchKernelGGL((ffn_down_mfma<2, LIST>), grid, dim3(kThreads), 0, st, a);
+    } else {
+        if (lds) hipLaunchKernelGGL((ffn_down_mfma_lds<1, LIST>), grid, dim3(kThreads), bytes, st, a);
+        else hipLaunchKernelGGL((ffn_down_mfma<1, LIST>), grid, dim3(kThreads), 0, st, a);
+    }
+}
+
 int launch_mfma(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
     // two 16-row tiles per wave when that still leaves >= 1024 workgroups
     constexpr int NT = 2;
@@ -1756,13 +1757,8 @@ int launch_mfma(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_
     const dim3 dgrid(unsigned(s.n_rb * s.ng));
     const unsigned dlds = unsigned(kWaves * s.dn_nt * 16 * kLdsPadU4 * sizeof(uint4));
     const bool dn_lds = kMfmaDownLds && a.I % 128 == 0;
-    if (s.dn_nt == 2) {
-        if (dn_lds) hipLaunchKernelGGL((ffn_down_mfma_lds<2>), dgrid, dim3(kThreads), dlds, st, a);
-        else hipLaunchKernelGGL((ffn_down_mfma<2>), dgrid, dim3(kThreads), 0, st, a);
-    } else {
-        if (dn_lds) hipLaunchKernelGGL((ffn_down_mfma_lds<1>), dgrid, dim3(kThreads), dlds, st, a);
-        else hipLaunchKernelGGL((ffn_down_mfma<1>), dgrid, dim3(kThreads), 0, st, a);
-    }
+    if (s.tile_up) launch_down_mfma<true>(a, s.dn_nt, dn_lds, dgrid, dlds, st);
+    else launch_down_mfma<false>(a, s.dn_nt, dn_lds, dgrid, dlds, st);
     STMOE_LAUNCHED();
     if (s.ng > 1) {
         const int n4 = a.B * a.H / 4;   // H is a multiple of 64
@@ -1816,7 +1812,7 @@ FfnArgs ffn_args(const void* x, const int32_t* idx, const float* w, int B, int K
 // (ffn_route_plan).
 bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
-    return s.mfma || s.tile;
+    return s.tile_up || s.tile;
 }
 
 // Whether the gate/up launch of these shapes can run the whole router: batch
