@@ -52,11 +52,17 @@ constexpr int kMaxH = 16384;
 // separate router tail costs less than the larger prologue)
 constexpr int kRouteInFfnMax = 128;
 
-// router bytes (E rows of H) up to which the batch-1 gate/up kernel computes
-// the logits too: every workgroup reads the whole router, and a launch less is
-// worth more where that is one or two loads per lane (E 8, H 256 fp32, 8 KiB:
-// 15.9 us a layer with the router launch); only while the grid is one
-// round of workgroups
+// The batch-1 gate/up kernel computes the router's logits too where that costs
+// its workgroups less than a launch: each wave takes every fourth expert, one
+// after the other (load, sum over the wave), so the bound is on the rows per
+// wave; and every workgroup reads the whole router, so also on its bytes.  Only
+// while the grid is one round of workgroups.  us a token of 4 layers, so / with
+// the router launch, calls as issued (as a replayed graph):
+//   E  8 H  256 fp32   56 /  72  (110 / 111)   E  16 H 256 bf16   56 /  72  (117 / 120)
+//   E  4 H 2048 bf16   65 /  69  (131 / 140)   E   2 H 2048 fp32  72 /  72  (139 / 143)
+//   E 32 H  256 bf16   58 /  71  (129 / 118)   E  64 H  64 fp32   74 /  72  (141 / 123)
+//   E 64 H  128 bf16   84 /  72  (151 / 123)   E 128 H  64 bf16  136 /  70  (200 / 132)
+constexpr int kRouterInFfnMaxE = 16;
 constexpr int kRouterInFfnBytes = 16384;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

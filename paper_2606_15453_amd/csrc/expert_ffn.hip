@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gate_up_b1(FfnArgs a, int blocks
     __shared__ float prob[kWaves][kMaxK];
     float wj = 1.f;
     int n_routed = 0;
-    __shared__ float zs[kMaxE];
+    __shared__ float zs[kRouterInFfnMaxE];
     const float* z = a.logits;
     if (a.router) {
         const int chunks = a.H * esz / 16;
@@ -1818,7 +1818,8 @@ bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype) 
 // Whether the gate/up launch of these shapes can run the whole router: batch
 // 1, a small router, and one round of workgroups.
 bool ffn_takes_router(int B, int K, int H, int I, int E, int n_shared, int dtype) {
-    if (B != 1 || size_t(E) * H * (dtype == STMOE_BF16 ? 2 : 4) > size_t(kRouterInFfnBytes)) return false;
+    if (B != 1 || E > kRouterInFfnMaxE || size_t(E) * H * (dtype == STMOE_BF16 ? 2 : 4) > size_t(kRouterInFfnBytes))
+        return false;
     const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
     const int rows = kWaves * (64 / s.gu_G);
     return (I + rows - 1) / rows * s.slots <= 1024;

@@ -49,7 +49,7 @@ __device__ __forceinline__ uint32_t order_key(float v) {
 
 // One token's logit of one expert by one wave: the steps and the order of
 // expert_logits below (its four waves' sums one after the other), so the bits
-// are the same.  For routers that fit a workgroup's prologue.
+// are the same.  For routers of few rows, computed in a workgroup's prologue.
 template <bool BF16>
 __device__ __forceinline__ float wave_logit(const uint4* wrow, const uint4* x, int chunks) {
     const int lane = threadIdx.x & 63;

@@ -239,13 +239,20 @@ def test_decode_plan_from_the_router_tail(over):
                                          (dict(E=65, K=4, B=1, T=4, P=2, C=10), False),
                                          (dict(E=32, K=4, B=1, T=4, P=2, C=10, dtype="bf16"), True),
                                          (dict(E=16, K=16, B=1, T=3, P=2, C=16), True),
-                                         (dict(E=2, K=1, B=1, T=4, P=2, C=1), False)])
+                                         (dict(E=2, K=1, B=1, T=4, P=2, C=1), False),
+                                         (dict(E=2, K=1, H=2048, I=64, B=1, T=3, P=2, C=1), False),
+                                         (dict(E=3, K=2, H=1032, I=72, B=1, T=3, P=2, C=2), True),
+                                         (dict(E=7, K=2, H=1032, I=72, B=1, T=3, P=2, C=3, dtype="bf16"), False),
+                                         (dict(E=16, K=3, H=512, I=64, B=1, T=3, P=2, C=5, dtype="bf16"), True),
+                                         (dict(E=17, K=3, H=64, I=64, B=1, T=3, P=2, C=5, dtype="bf16"), False),
+                                         (dict(E=64, K=8, H=128, I=64, B=1, T=3, P=2, C=12, dtype="bf16"), True)])
 def test_decode_resident_edge_shapes(over, renorm):
-    """The FFN's in-kernel gating at its edges: E not a multiple of 4 (padded
-    keys), B*E = 256 (the largest routed in-kernel), renormalised weights; at
-    batch 1 the gating in registers of the batch-1 gate/up kernel (E up to 64,
-    K up to 16, shared experts, bf16) and above 64 experts the LDS prologue.
-    Selections, outputs and hit counts as in the oracle; the capped run (router
+    """The FFN's in-kernel gating at its edges: E not a multiple of 4, a batch
+    beyond it, renormalised weights; at batch 1 the gating in registers (E up
+    to 65, K up to 16, shared experts, bf16) and the whole router inside the
+    gate/up kernel (rows of 512 and 258 chunks: all four partial sums, the
+    second chunk of a step and its remainder; of 129 and 64; E 16, the most it
+    takes, and 17).  Selections, outputs and hit counts as in the oracle; the capped run (router
     tail kernel, selection passed to the FFN) gives bit-identical outputs."""
     from gpuhelp import rel_l2
     from oracle.stmoe_oracle import MODE_STMOE
@@ -266,6 +273,48 @@ def test_decode_resident_edge_shapes(over, renorm):
     _, ys_cap, _, _ = _run_gpu(st, 1, capped=True, renorm=renorm)
     for t in range(cfg.T):
         assert np.array_equal(ys_cap[t], ys[t]), t
+
+
+def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
+    """Kernel launches of one resident decode layer without a predictor,
+    counted in a captured graph (every node of it is a launch)."""
+    import ctypes
+    import torch
+    from gpuhelp import DEV
+    from paper_2606_15453_amd import stmoe as S
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    w = torch.zeros((E + n_shared, 3 * H * I), dtype=dt, device=DEV)
+    ptrs = [w[e].data_ptr() for e in range(E + n_shared)]
+    router, x = torch.zeros((E, H), dtype=dt, device=DEV), torch.zeros((B, H), dtype=dt, device=DEV)
+    y = torch.zeros((B, H), dtype=torch.float32, device=DEV)
+    st = torch.cuda.Stream()
+    ctx = S.DecodeContext(1, E, K, B, H, I, S.BF16 if dtype == "bf16" else S.F32, [router.data_ptr()],
+                          resident_ptrs=ptrs[:E], shared_ptrs=ptrs[E:], n_shared=n_shared, stream=st)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=st):
+        ctx.layer(0, 0, x, y, mode=S.MODE_ON_DEMAND)
+    n = ctypes.c_size_t(0)
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    rc = hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n))
+    assert rc == 0
+    ctx.close()
+    return n.value
+
+
+@pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,n", [
+    # batch 1: a router of up to 16 rows and 16 KiB runs inside the gate/up launch
+    (1, 2, 8, 256, 512, 0, "f32", 2), (1, 2, 16, 256, 512, 0, "f32", 2), (1, 2, 16, 512, 512, 1, "bf16", 2),
+    (1, 2, 17, 64, 256, 0, "bf16", 3), (1, 4, 64, 64, 256, 0, "f32", 3), (1, 8, 128, 64, 256, 0, "bf16", 3),
+    (1, 2, 8, 520, 512, 0, "f32", 3),
+])
+def test_layer_launches(B, K, E, H, I, n_shared, dtype, n):
+    """Where the router's work runs, by the launches of a layer: none in front
+    of the two FFN launches where all of it runs inside the first; the logits
+    alone; or logits and the tail that selects (16-row tiles sum partial
+    results in a launch more)."""
+    assert _kernels_per_layer(B, K, E, H, I, n_shared, dtype) == n
 
 
 @pytest.mark.parametrize("name,over,mode", [("tiny", dict(T=8), 2), ("tiny", dict(T=8), 3),
