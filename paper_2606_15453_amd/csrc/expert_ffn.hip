@@ -121,17 +121,30 @@ struct PlanB : Plan {
     const char* blob[kMaxSlots];
 };
 
-// Gating (Section 2) inside a gate/up workgroup: the router tail's row, one
-// wave per row, into the plan's idx/w; block 0 also publishes them.
+// Gating (Section 2) inside a gate/up workgroup: the same steps and
+// arithmetic as the router tail, on rows of E rounded up to 4, into the
+// plan's idx/w; block 0 also publishes them.
 __device__ void route_into_plan(const FfnArgs& a, Plan& p) {
+    constexpr int kRouteRows = kRouteInFfnMax + 3 * kMaxB;
+    __shared__ __align__(16) uint32_t keys[kRouteRows];
+    __shared__ float zl[kRouteRows];
+    __shared__ int32_t win[kMaxB * kMaxK];
+    __shared__ float rowmax[kMaxB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = (a.E + 3) & ~3;
+    gating::stage_keys(a.logits, a.B, a.E, row, keys, zl);
+    gating::rank_winners(keys, zl, a.B, a.E, a.K, row, win, rowmax);
     for (int b = wave; b < a.B; b += kWaves) {
         int e;
         float wt;
-        gating::route_row(a.logits + size_t(b) * a.E, a.E, a.K, a.renorm, p.idx + b * a.K, p.w + b * a.K, e, wt);
-        if (blockIdx.x == 0 && lane < a.K) {
-            const_cast<int32_t*>(a.idx)[b * a.K + lane] = e;
-            const_cast<float*>(a.w)[b * a.K + lane] = wt;
+        gating::row_weights(zl, win, rowmax, b, a.E, a.K, row, a.renorm, e, wt);
+        if (lane < a.K) {
+            p.idx[b * a.K + lane] = e;
+            p.w[b * a.K + lane] = wt;
+            if (blockIdx.x == 0) {
+                const_cast<int32_t*>(a.idx)[b * a.K + lane] = e;
+                const_cast<float*>(a.w)[b * a.K + lane] = wt;
+            }
         }
     }
 }

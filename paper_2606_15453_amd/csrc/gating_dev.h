@@ -194,8 +194,9 @@ __device__ __forceinline__ void topk_positions(const uint32_t (&key)[kKeyRegs], 
 }
 
 // Softmax and top-K of one batch row by one wave, in registers.  The router
-// tail and the expert FFN's routing prologue both run this, so their
-// selections and weights are bit-identical.  Each wave works alone: no barrier.
+// tail and the routing prologue of the batch-1 and 4-row FFN kernels run this,
+// so their selections and weights are bit-identical.  Each wave works alone: no
+// barrier.
 //
 // z [E] (global or LDS); sel [K], prob [K]: this row's, in LDS.  Lanes k < K
 // return the expert and weight of position k; sel/prob hold them as well.
@@ -259,6 +260,103 @@ __device__ __forceinline__ void route_row(const float* z, int E, int K, int reno
         sel[lane] = e;
         prob[lane] = wt;
     }
+}
+
+// The same for a few short rows by a whole workgroup, in three steps that share
+// LDS buffers passed by the caller (rows of `row` >= E rounded up to 4 entries):
+//   stage_keys   logits -> order keys and values in LDS
+//   rank_winners for each (row, expert) pair, T lanes split the row and count
+//                the experts that beat it (larger key, or equal key and lower
+//                index): a count below K is its output position
+//   row_weights  one wave per row: softmax sum and the K weights.
+// Keys, ranks and the order of every sum are route_row's, so the selections and
+// weights are bit-identical.  For the prologue of the FFN kernels that hold a
+// whole plan: route_row takes rows in turn per wave (E 12, batch 9: 4.8 us of
+// the gate/up launch's 24.8), and inlined there its registers cost every call
+// a wave per SIMD, also those that don't route (E 11 H 512 I 1664, batch 2:
+// gate/up 12.3 us, 10.4 with these steps).
+
+// Keys padded with 0 up to a multiple of 4: a pad never beats a real key
+// and never ties with a lower index.  Ends with a barrier.
+__device__ void stage_keys(const float* z, int B, int E, int row, uint32_t* keys, float* zl) {
+    const int E4 = (E + 3) & ~3;
+    for (int i = threadIdx.x; i < B * E4; i += kThreads) {
+        const int b = i / E4, f = i - b * E4;
+        const float v = f < E ? z[b * E + f] : 0.f;
+        keys[b * row + f] = f < E ? order_key(v) : 0u;
+        zl[b * row + f] = v;
+    }
+    __syncthreads();
+}
+
+// win [B][K]: selected experts by position; rowmax [B].  Ends with a barrier.
+// The scan counts greater and equal keys (four row entries per LDS read,
+// four reads in flight); only a lane that met an equal key other than its
+// own rescans its row for equal keys at lower indices.
+__device__ void rank_winners(const uint32_t* keys, const float* zl, int B, int E, int K, int row,
+                             int32_t* win, float* rowmax) {
+    const int tid = threadIdx.x, BE = B * E;
+    int T = 1;                                    // lanes per pair (power of two)
+    while (T < 16 && BE * T * 2 <= kThreads) T *= 2;
+    const int n4 = ((E + 3) & ~3) / 4;
+    for (int base = 0; base < BE * T; base += kThreads) {
+        const int t = base + tid, i = t / T, part = t & (T - 1);
+        const int b = i / E, f = i - b * E;
+        int gt = 0, eq = 0;
+        const uint32_t* rk = keys + b * row;
+        const uint32_t mine = i < BE ? rk[f] : 0u;
+        if (i < BE) {
+            int c = part;
+            for (; c + 3 * T < n4; c += 4 * T) {
+                uint4 k[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) k[u] = *reinterpret_cast<const uint4*>(rk + 4 * (c + u * T));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    gt += int(k[u].x > mine) + int(k[u].y > mine) + int(k[u].z > mine) + int(k[u].w > mine);
+                    eq += int(k[u].x == mine) + int(k[u].y == mine) + int(k[u].z == mine) + int(k[u].w == mine);
+                }
+            }
+            for (; c < n4; c += T) {
+                const uint4 k = *reinterpret_cast<const uint4*>(rk + 4 * c);
+                gt += int(k.x > mine) + int(k.y > mine) + int(k.z > mine) + int(k.w > mine);
+                eq += int(k.x == mine) + int(k.y == mine) + int(k.z == mine) + int(k.w == mine);
+            }
+        }
+        for (int o = 1; o < T; o <<= 1) {
+            gt += __shfl_xor(gt, o, 64);
+            eq += __shfl_xor(eq, o, 64);
+        }
+        if (i < BE && part == 0) {
+            int cnt = gt;
+            if (eq > 1)                           // ties: equal keys at lower indices rank higher
+                for (int g = 0; g < f; ++g) cnt += rk[g] == mine;
+            if (cnt < K) {
+                win[b * K + cnt] = f;
+                if (cnt == 0) rowmax[b] = zl[b * row + f];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Softmax weights of the winners (NaN-free logits assumed): lanes k < K of
+// the row's wave get (expert, weight) of position k.  Whole wave calls it.
+__device__ __forceinline__ void row_weights(const float* zl, const int32_t* win, const float* rowmax, int b,
+                                            int E, int K, int row, int renorm, int& e, float& wt) {
+    const int lane = threadIdx.x & 63;
+    const float m = rowmax[b];
+    float s = 0.f;
+    for (int f = lane; f < E; f += 64) s += expf(zl[b * row + f] - m);
+    s = wave_sum(s);
+    float p = 0.f;
+    e = 0;
+    if (lane < K) {
+        e = win[b * K + lane];
+        p = expf(zl[b * row + e] - m) / s;
+    }
+    const float wsum = wave_sum(p);
+    wt = renorm ? p / wsum : p;
 }
 
 // The router tail, one wave per batch row: writes idx/w (and leaves the
