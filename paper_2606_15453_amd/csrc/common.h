@@ -49,7 +49,8 @@ constexpr int kMaxB = 16;
 constexpr int kMaxH = 16384;
 // batch x experts up to which the expert FFN's gate/up kernel runs the
 // gating itself (every gate/up workgroup ranks the logits, so beyond this the
-// separate router tail costs less than the larger prologue)
+// separate router tail costs less than the larger prologue; on 4-row tiles it
+// does so earlier, see ffn_takes_plan)
 constexpr int kRouteInFfnMax = 128;
 
 // The batch-1 gate/up kernel computes the router's logits too where that costs

@@ -438,8 +438,8 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
     }
 
     // R + V + P.  Without a cache: the router on the compute stream (for
-    // B*E <= 128 only its logits: the FFN's gate/up kernel does softmax and
-    // top-K), then verify/update and prediction on the side stream, off the
+    // B*E <= 128, unless its tail makes the FFN's plan, only its logits: the
+    // FFN's gate/up kernel does softmax and top-K), then verify/update and prediction on the side stream, off the
     // FFN's path.
     // Side work still queued reads selections of this token's layers and the
     // next one's; in the usual layer order it can only collide with this
@@ -450,9 +450,8 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         STMOE_HIP(hipStreamWaitEvent(c->s, c->ev_side, 0));
         c->side_pending = false;
     }
-    const bool takes_plan = !c->cache && ffn_takes_plan(B, K, c->H, c->I, E, c->n_shared, c->dtype);
-    const bool route_in_ffn = !c->cache && B * E <= kRouteInFfnMax;
-    const bool plan = takes_plan && !route_in_ffn;
+    const bool plan = !c->cache && ffn_takes_plan(B, K, c->H, c->I, E, c->n_shared, c->dtype);
+    const bool route_in_ffn = !c->cache && !plan && B * E <= kRouteInFfnMax;
     const void* ebase = c->rbase.empty() ? nullptr : c->rbase[size_t(layer)];
     const void* const* sptr = c->n_shared ? c->shared + size_t(layer) * c->n_shared : nullptr;
     float* zbuf = reinterpret_cast<float*>(c->route_ws);

@@ -1439,6 +1439,8 @@ struct Shape {
     bool mfma;          // 16-row MFMA path (batch > 8)
     bool tile;          // 4-row tile path
     bool tile_up;       // 16-row MFMA path: gate/up on 4-row tiles
+    bool up_split;      // 4-row gate/up: a workgroup's waves split the columns of 4 rows
+    int up_blocks;      // 4-row gate/up: workgroups per slot
     int slots;          // slot capacity
     int gu_G;           // GEMV gate/up lanes per row
     int dn_kind;        // 0: rows (lane groups, slots split over waves), 1: whole-workgroup rows, 2: MFMA,
@@ -1451,6 +1453,8 @@ struct Shape {
     int dn_R;           // rows per lane group of the GEMV down kernel
 };
 
+constexpr int kRouteTileMaxB = 4;             // 4-row gate/up routes itself up to this batch ...
+constexpr int kRouteTileMaxBlocks = 4096;     // ... and this many workgroups (ffn_takes_plan)
 constexpr int kDownRowsWgTarget = 1024;  // lane-group down: fewest workgroups more rows per group may leave
 constexpr int kDownWgR = 4;   // rows per workgroup (whole-workgroup down)
 constexpr int kDownForceG = 0;  // lanes per down row (0: by row length)
@@ -1522,6 +1526,17 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // H 1024 I 704 at batch 3 fp32 24.4 against 22.9.
     const bool few = H <= 1024 && H % 128 == 0 && (B == 2 || (dtype == STMOE_F32 && B <= 4 && I >= 2 * H));
     s.tile = B >= 2 && !s.mfma && !few && (dtype == STMOE_F32 || act16);
+    // Split the columns over the waves where each wave keeps two steps of them
+    // (DeepSeek-V2-Lite shapes at batch 4: 43.2 us split, 47.6 not; rows of
+    // 1408 bytes at batch 14, gate/up + down: 49.5 against 36.2).
+    // With four token groups a split tile's share is not worth its prologue
+    // (gate/up + down: Qwen3-30B shapes, batch 16, 134 us split with the plan
+    // ready, 163 without, 127 not split; Qwen3-235B shapes 460, 496, 466).  The
+    // rule must not ask for the plan: the same layer runs with and without one
+    // (resident and cached) and gives the same bits.
+    s.up_split = B <= 8 && H * esz >= 2 * kWaves * 256;
+    const int up_rows = s.up_split ? 4 : 4 * kWaves;
+    s.up_blocks = (I + up_rows - 1) / up_rows;
     if (s.tile) {
         s.dn_kind = 3;
         return s;
@@ -1654,21 +1669,16 @@ int launch_gemv_b(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t e
 // -------------------------------------------------------------- tile kernels
 
 template <bool BF, int TG>
-void launch_up_tile(const FfnArgs& a, hipStream_t st) {
+void launch_up_tile(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const int extra = a.ready ? 0 : 1;       // the workgroup that publishes the plan
-    // split the columns over the waves where each wave keeps two steps of them
-    // (DeepSeek-V2-Lite shapes at batch 4: 43.2 us split, 47.6 not; rows of
-    // 1408 bytes at batch 14, gate/up + down: 49.5 against 36.2)
-    // With four token groups a split tile's share is not worth its prologue
-    // (gate/up + down: Qwen3-30B shapes, batch 16, 134 us split with the plan
-    // ready, 163 without, 127 not split; Qwen3-235B shapes 460, 496, 466).  The
-    // rule must not ask for the plan: the same layer runs with and without one
-    // (resident and cached) and gives the same bits.
-    const bool sk = TG < 4 && a.H * (BF ? 2 : 4) >= 2 * kWaves * 256;
-    const int rows = sk ? 4 : 4 * kWaves, bps = (a.I + rows - 1) / rows;
-    const dim3 grid(unsigned(bps * a.cap + extra));
-    if (sk) hipLaunchKernelGGL((ffn_up_tile<BF, TG, true>), grid, dim3(kThreads), 0, st, a, bps);
-    else hipLaunchKernelGGL((ffn_up_tile<BF, TG, false>), grid, dim3(kThreads), 0, st, a, bps);
+    const dim3 grid(unsigned(s.up_blocks * a.cap + extra));
+    if constexpr (TG < 4) {
+        if (s.up_split) {
+            hipLaunchKernelGGL((ffn_up_tile<BF, TG, true>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((ffn_up_tile<BF, TG, false>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
 }
 
 template <bool BF, int RQ, int TG, int W>
@@ -1702,8 +1712,8 @@ void launch_down_tile(const FfnArgs& a, hipStream_t st) {
 }
 
 template <bool BF, int TG>
-int launch_tile_t(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
-    launch_up_tile<BF, TG>(a, st);
+int launch_tile_t(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
+    launch_up_tile<BF, TG>(a, s, st);
     STMOE_LAUNCHED();
     if (ev_mid) STMOE_HIP(hipEventRecord(ev_mid, st));
     launch_down_tile<BF, TG>(a, st);
@@ -1712,10 +1722,10 @@ int launch_tile_t(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
 }
 
 template <bool BF>
-int launch_tile(const FfnArgs& a, hipStream_t st, hipEvent_t ev_mid) {
-    if (a.B <= 4) return launch_tile_t<BF, 1>(a, st, ev_mid);
-    if (a.B <= 8) return launch_tile_t<BF, 2>(a, st, ev_mid);
-    return launch_tile_t<BF, 4>(a, st, ev_mid);
+int launch_tile(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_mid) {
+    if (a.B <= 4) return launch_tile_t<BF, 1>(a, s, st, ev_mid);
+    if (a.B <= 8) return launch_tile_t<BF, 2>(a, s, st, ev_mid);
+    return launch_tile_t<BF, 4>(a, s, st, ev_mid);
 }
 
 template <bool LIST>
@@ -1734,7 +1744,7 @@ int launch_mfma(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t ev_
     constexpr int NT = 2;
     const int rows = kWaves * NT * 16;
     if (s.tile_up) {
-        launch_up_tile<true, 4>(a, st);
+        launch_up_tile<true, 4>(a, s, st);
     } else if ((a.I / (kWaves * 16)) * s.slots < kMfmaSplitKBelow && a.H % 256 == 0) {
         const int bps = a.I / 16;
         if (kMfmaUpLds && a.H % 512 == 0) {
@@ -1821,11 +1831,20 @@ FfnArgs ffn_args(const void* x, const int32_t* idx, const float* w, int B, int K
 }
 }  // namespace
 
-// Whether the FFN of these shapes can start from a plan made beforehand
-// (ffn_route_plan).
+// Whether the router's tail makes the plan of these shapes (ffn_route_plan) in
+// front of the FFN.  Small routers may run in the gate/up launch instead, a
+// launch less, but on 4-row tiles each workgroup then routes ahead of four
+// rows' weights: that pays up to four tokens (a row per wave) and a few rounds
+// of workgroups.  us a token of 4 layers, in the launch / in the tail:
+//   E 16 top-2 H 1024 I 1024, batch 4   98 / 102   E  8 top-2 H 1024 I 4096, batch 8    276 /  200
+//   E 33 top-2 H 1728 I  512, batch 3   86 /  95   E 16 top-4 H 2048 I 2048, batch 8    374 /  299
+//   E 40 top-4 H 3072 I 1024, batch 3  199 / 203   E 30 top-4 + 2 H 2048 I 1408, batch 4  259 / 243
+//   E 16 top-4 H  512 I  512, batch 4   82 /  90   E  8 top-2 H 4096 I 14336, batch 8  1557 / 1454
+// (batch 5 to 16 otherwise 83 / 83 to 230 / 180, and 84 / 88 at E 8 H 384 I 640)
 bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
-    return s.tile_up || s.tile;
+    if (!s.tile_up && !s.tile) return false;
+    return B * E > kRouteInFfnMax || B > kRouteTileMaxB || s.up_blocks * s.slots > kRouteTileMaxBlocks;
 }
 
 // Whether the gate/up launch of these shapes can run the whole router: batch
@@ -1881,7 +1900,7 @@ int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, 
     a.ready = ready;
     a.router = router;
     if (s.mfma) return launch_mfma(a, s, st, ev_mid);
-    if (s.tile) return dtype == STMOE_BF16 ? launch_tile<true>(a, st, ev_mid) : launch_tile<false>(a, st, ev_mid);
+    if (s.tile) return dtype == STMOE_BF16 ? launch_tile<true>(a, s, st, ev_mid) : launch_tile<false>(a, s, st, ev_mid);
     return dtype == STMOE_BF16 ? launch_gemv_b<true>(a, s, st, ev_mid)
                                : launch_gemv_b<false>(a, s, st, ev_mid);
 }

@@ -308,6 +308,11 @@ def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
     (1, 2, 8, 256, 512, 0, "f32", 2), (1, 2, 16, 256, 512, 0, "f32", 2), (1, 2, 16, 512, 512, 1, "bf16", 2),
     (1, 2, 17, 64, 256, 0, "bf16", 3), (1, 4, 64, 64, 256, 0, "f32", 3), (1, 8, 128, 64, 256, 0, "bf16", 3),
     (1, 2, 8, 520, 512, 0, "f32", 3),
+    # 4-row tiles: the router's tail makes the plan beyond four tokens or 4096 workgroups
+    (4, 2, 16, 256, 512, 0, "bf16", 3), (5, 2, 16, 256, 512, 0, "bf16", 4), (8, 4, 16, 256, 64, 0, "bf16", 4),
+    (4, 4, 16, 2048, 1024, 0, "bf16", 3), (4, 4, 16, 2048, 1032, 0, "bf16", 4),
+    # 16-row tiles up to B * E = 128 route in their gate/up launch (and sum partial results in one more)
+    (9, 4, 8, 256, 64, 0, "bf16", 4),
 ])
 def test_layer_launches(B, K, E, H, I, n_shared, dtype, n):
     """Where the router's work runs, by the launches of a layer: none in front
