@@ -1453,6 +1453,7 @@ struct Shape {
     int dn_R;           // rows per lane group of the GEMV down kernel
 };
 
+constexpr int kUpSplitMaxBlocks = 640;        // 4-row gate/up: short rows are split up to this many workgroups unsplit
 constexpr int kRouteTileMaxB = 4;             // 4-row gate/up routes itself up to this batch ...
 constexpr int kRouteTileMaxBlocks = 4096;     // ... and this many workgroups (ffn_takes_plan)
 constexpr int kDownRowsWgTarget = 1024;  // lane-group down: fewest workgroups more rows per group may leave
@@ -1526,15 +1527,22 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // H 1024 I 704 at batch 3 fp32 24.4 against 22.9.
     const bool few = H <= 1024 && H % 128 == 0 && (B == 2 || (dtype == STMOE_F32 && B <= 4 && I >= 2 * H));
     s.tile = B >= 2 && !s.mfma && !few && (dtype == STMOE_F32 || act16);
-    // Split the columns over the waves where each wave keeps two steps of them
-    // (DeepSeek-V2-Lite shapes at batch 4: 43.2 us split, 47.6 not; rows of
-    // 1408 bytes at batch 14, gate/up + down: 49.5 against 36.2).
+    // Split the columns over the waves where each wave keeps enough of them for
+    // its share of a workgroup's prologue, 14 steps a row (DeepSeek-V2-Lite
+    // shapes at batch 4: 43.2 us split, 47.6 not; E 12 top-3 H 1920 I 1664, batch
+    // 4: 23.1 and 25.6), or, down to two steps a wave, where the launch has few
+    // workgroups otherwise (E 18 top-5 + 2 H 1536 I 512, batch 8: 16.5 and 18.2).
+    // Not for short rows in many of them (batch 8: E 32 top-8 H 1024 I 1024 32.5
+    // split, 22.2 not; E 43 top-4 H 1024 I 1920 52.2 and 35.8; E 68 top-8 + 2
+    // H 1280 I 2176 108.5 and 74.8; batch 3, E 16 top-6 + 1 H 1664 I 4096 63.6
+    // and 52.5).
     // With four token groups a split tile's share is not worth its prologue
     // (gate/up + down: Qwen3-30B shapes, batch 16, 134 us split with the plan
     // ready, 163 without, 127 not split; Qwen3-235B shapes 460, 496, 466).  The
     // rule must not ask for the plan: the same layer runs with and without one
     // (resident and cached) and gives the same bits.
-    s.up_split = B <= 8 && H * esz >= 2 * kWaves * 256;
+    s.up_split = B <= 8 && (H * esz >= 14 * 256 ||
+                            (H * esz >= 2 * kWaves * 256 && (I + 15) / 16 * s.slots <= kUpSplitMaxBlocks));
     const int up_rows = s.up_split ? 4 : 4 * kWaves;
     s.up_blocks = (I + up_rows - 1) / up_rows;
     if (s.tile) {

@@ -49,3 +49,30 @@ def expert_f64(cfg, l, e, shared=False):
 
 def ptr_array(ptrs) -> torch.Tensor:
     return torch.tensor([int(p) for p in ptrs], dtype=torch.int64, device=DEV)
+
+
+def graph_launches(fn, stream):
+    """The kernel launches of fn() on `stream`, captured and not run:
+    [(workgroups, threads per workgroup)] in order."""
+    import ctypes as C
+
+    class Params(C.Structure):       # hipKernelNodeParams
+        _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3),
+                    ("params", C.c_void_p), ("shared", C.c_uint32)]
+
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=stream):
+        fn()
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    graph, n = C.c_void_p(g.raw_cuda_graph()), C.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        out.append((p.grid[0] * p.grid[1] * p.grid[2], p.block[0] * p.block[1] * p.block[2]))
+    return out

@@ -276,11 +276,9 @@ def test_decode_resident_edge_shapes(over, renorm):
 
 
 def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
-    """Kernel launches of one resident decode layer without a predictor,
-    counted in a captured graph (every node of it is a launch)."""
-    import ctypes
+    """Kernel launches of one resident decode layer without a predictor."""
     import torch
-    from gpuhelp import DEV
+    from gpuhelp import DEV, graph_launches
     from paper_2606_15453_amd import stmoe as S
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     w = torch.zeros((E + n_shared, 3 * H * I), dtype=dt, device=DEV)
@@ -290,17 +288,9 @@ def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
     st = torch.cuda.Stream()
     ctx = S.DecodeContext(1, E, K, B, H, I, S.BF16 if dtype == "bf16" else S.F32, [router.data_ptr()],
                           resident_ptrs=ptrs[:E], shared_ptrs=ptrs[E:], n_shared=n_shared, stream=st)
-    torch.cuda.synchronize()
-    g = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(g, stream=st):
-        ctx.layer(0, 0, x, y, mode=S.MODE_ON_DEMAND)
-    n = ctypes.c_size_t(0)
-    with open("/proc/self/maps") as f:
-        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
-    rc = hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n))
-    assert rc == 0
+    n = len(graph_launches(lambda: ctx.layer(0, 0, x, y, mode=S.MODE_ON_DEMAND), st))
     ctx.close()
-    return n.value
+    return n
 
 
 @pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,n", [

@@ -190,6 +190,8 @@ def test_ffn_repeated_and_out_of_range_entries(name, row):
     (16, 2, 5, 64, 8, 8, "f32"),         # the largest batch, eight shared experts
     (16, 16, 256, 128, 64, 0, "bf16"),   # the largest K and E: 16-row down after 4-row gate/up
     (16, 4, 8, 128, 64, 0, "bf16"),      # many tokens per slot: 16-row gate/up
+    (8, 5, 18, 1032, 264, 1, "f32"),     # short rows in few workgroups: split columns, remainder, two token groups
+    (3, 3, 20, 1608, 1192, 1, "bf16"),   # ... in many: not split, 12 steps and a remainder
 ])
 def test_ffn_tile_edges(B, K, E, H, I, n_shared, dtype):
     """The 4-row tile kernels at the edges of their tiles, token groups and
@@ -236,3 +238,30 @@ def test_ffn_non_finite_weights_stay_with_their_tokens(B, dtype, H, I):
             assert np.array_equal(ys[0][b], ys[1][b]), b
         else:
             assert not np.isfinite(ys[1][b]).any(), b
+
+
+def _ffn_launches(B, K, E, H, I, n_shared, dtype):
+    import torch
+    from gpuhelp import DEV, graph_launches, ptr_array
+    from paper_2606_15453_amd import stmoe as S
+    dt, sdt = (torch.bfloat16, S.BF16) if dtype == "bf16" else (torch.float32, S.F32)
+    x = torch.zeros((B, H), dtype=dt, device=DEV)
+    idx, w = torch.zeros((B, K), dtype=torch.int32, device=DEV), torch.zeros((B, K), device=DEV)
+    y = torch.zeros((B, H), device=DEV)
+    ws = torch.zeros(S.ffn_workspace_bytes(B, K, E, H, I, n_shared, sdt), dtype=torch.uint8, device=DEV)
+    table, st = ptr_array([x.data_ptr()] * (E + n_shared)), torch.cuda.Stream()      # captured, not run
+    return graph_launches(lambda: S.expert_ffn(x, idx, w, H, I, E, sdt, table, y, ws, shared_ptrs=table if n_shared else None,
+                                               n_shared=n_shared, stream=st), st)
+
+
+@pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,rows", [
+    (8, 8, 32, 1024, 1024, 0, "bf16", 16), (8, 4, 43, 1024, 1920, 0, "bf16", 16), (3, 6, 16, 1664, 4096, 1, "bf16", 16),
+    (5, 4, 157, 640, 1152, 0, "f32", 16), (4, 6, 64, 2048, 1408, 2, "bf16", 4), (8, 5, 18, 1536, 512, 2, "bf16", 4),
+    (8, 4, 8, 256, 64, 0, "bf16", 16),
+])
+def test_gate_up_tile_splits(B, K, E, H, I, n_shared, dtype, rows):
+    """Rows per gate/up workgroup of the 4-row tiles: columns split over its
+    waves (4 rows) for long rows, and for shorter ones in few workgroups."""
+    slots = min(B * K, E) + n_shared
+    up = _ffn_launches(B, K, E, H, I, n_shared, dtype)[0]
+    assert up == (-(-I // rows) * slots + 1, 256)        # one more publishes the plan
