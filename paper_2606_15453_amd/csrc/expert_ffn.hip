@@ -27,7 +27,7 @@
 // row block (split-K over its four waves).
 // Batch 2 to 8, and fp32 weights or ragged sizes beyond: 4-row tiles on the
 // 16-block 4x4 MFMA (ffn_tile.h): a step costs a slot's own tokens.
-// Batch > 8: 16-row tiles (v_mfma_f32_16x16x32_bf16).  The tokens form the
+// Batch > 8, and 8 where slots serve many tokens: 16-row tiles (v_mfma_f32_16x16x32_bf16).  The tokens form the
 // 16-row A operand (padded with zeros), 16 weight rows the B operand.  In
 // each 64-element step lane (n, q) loads elements 8q..8q+7 and 32+8q..32+8q+7
 // of row n, so every load instruction reads 16 full 64-byte row segments.
@@ -61,7 +61,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kMaxShared = 8;
 constexpr int kMaxSlots = kMaxE + kMaxShared;
 constexpr int kDownWgTarget = 256;    // workgroups the MFMA down phase aims for
-constexpr int kMfmaMinB = 9;          // batch from which the 16-row MFMA kernels run
+constexpr int kMfmaMinB = 9;          // batch from which the 16-row MFMA kernels run (batch 8: plan_shape)
 constexpr int kUpInFlight = 2;        // 16-byte chunks per row in flight per lane (GEMV gate/up)
 constexpr bool kUpB1 = true;           // batch 1: the gate/up kernel that finds its slot in registers
 constexpr int kShortRowChunks = 4;    // down rows with at most this many chunks per lane are short: ...
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(kThreads) void ffn_down_wg(FfnArgs a) {
 }
 
 // ============================================================================
-// 16-row MFMA path (batch > 8, bf16, H and I multiples of 64)
+// 16-row MFMA path (batch > 8 and some of 8, bf16, H and I multiples of 64)
 // ============================================================================
 
 // The slots of a 16-row down workgroup: from the list that a gate/up launch on
@@ -1436,7 +1436,7 @@ int pick_group(int chunks) {
 }
 
 struct Shape {
-    bool mfma;          // 16-row MFMA path (batch > 8)
+    bool mfma;          // 16-row MFMA path (batch 8 and more)
     bool tile;          // 4-row tile path
     bool tile_up;       // 16-row MFMA path: gate/up on 4-row tiles
     bool up_split;      // 4-row gate/up: a workgroup's waves split the columns of 4 rows
@@ -1477,7 +1477,18 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     Shape s{};
     const int esz = dtype == STMOE_BF16 ? 2 : 4;
     s.slots = (B * K < E ? B * K : E) + n_shared;
-    s.mfma = dtype == STMOE_BF16 && B >= kMfmaMinB && H % 64 == 0 && I % 64 == 0;
+    // The 16-row gate/up kernels that stage rows through LDS; the others keep
+    // too few bytes in flight to match the 4-row tiles.
+    const bool staged = H % 512 == 0 || (H % 128 == 0 && (H % 256 != 0 || I / 64 * s.slots >= kMfmaSplitKBelow));
+    // Batch 8 takes the 16-row tiles where slots serve many tokens over long
+    // rows: tokens per slot times H beyond 8192.  us per call, 16-row / 4-row:
+    //   E  8 top-4 H 4096 I  1024   38.2 /  43.4   E  8 top-2 H 4096 I 14336  444 / 417
+    //   E  8 top-8 H 4096 I  1024   39.5 /  52.5   E  8 top-4 H 2048 I  2048  45.3 / 45.6 (layer 59.5 / 55.1)
+    //   E  8 top-4 H 4096 I 14336  439.5 / 478.4   E 64 top-6 + 2 H 2048 I 1408  110.6 / 110.0
+    //   E  8 top-8 H 4096 I 14336  454.6 / 648.3   E  8 top-8 H 1024 I  4096  61.3 / 58.7
+    //   E 16 top-4 + 1 H 4096 I 1536  95.5 / 100.5   E 128 top-8 H 4096 I 1536  312 / 302
+    const bool full8 = B == 8 && staged && (long long)B * (K + n_shared) * H > 8192ll * s.slots;
+    s.mfma = dtype == STMOE_BF16 && (B >= kMfmaMinB || full8) && H % 64 == 0 && I % 64 == 0;
     // A 4-row tile costs one operand load and one product per four tokens of
     // a slot, a 16-row one the same for 1 to 16: few tokens per slot take the
     // former (Qwen3-235B shapes at batch 16, 1.6 per slot: gate/up 332 -> 313
