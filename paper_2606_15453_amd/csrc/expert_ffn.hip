@@ -1536,7 +1536,17 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // against 32.3 (bf16 there 20.9 against 19.6).  Beyond: E 16 H 2048 I 1024
     // at batch 2 15.8 against 15.4; E 60 H 520 I 264 11.9 against 10.2; E 32
     // H 1024 I 704 at batch 3 fp32 24.4 against 22.9.
-    const bool few = H <= 1024 && H % 128 == 0 && (B == 2 || (dtype == STMOE_F32 && B <= 4 && I >= 2 * H));
+    // Also two tokens in bf16 with up to three slots of long down rows (E 9 top-1
+    // H 416 I 1176: kernels 9.0 us against 10.2), and in fp32 with seven slots or
+    // more, beyond H 1280 where long down rows leave no lane idle (E 23 top-6
+    // H 1096 I 656 21.6 against 24.4, E 14 top-7 H 2560 I 1280 65.1 against 68.1,
+    // E 32 top-4 H 4096 I 1024 69.8 against 74.8; but E 31 top-1 + 2 H 888 I 2296
+    // 26.2 against 24.1, E 60 top-4 + 1 H 2056 I 1000 53.8 against 50.7, E 153
+    // top-4 H 3456 I 640 44.4 against 41.5).
+    const bool few2 = dtype == STMOE_F32 ? s.slots >= 7 && (H <= 1280 || (I >= 1024 && I % 256 == 0))
+                                         : s.slots <= 3 && H <= 1024 && I >= 2 * H;
+    const bool few = (H <= 1024 && H % 128 == 0 && (B == 2 || (dtype == STMOE_F32 && B <= 4 && I >= 2 * H))) ||
+                     (B == 2 && few2);
     s.tile = B >= 2 && !s.mfma && !few && (dtype == STMOE_F32 || act16);
     // Split the columns over the waves where each wave keeps enough of them for
     // its share of a workgroup's prologue, 14 steps a row (DeepSeek-V2-Lite

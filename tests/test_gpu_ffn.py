@@ -278,3 +278,21 @@ def test_batch8_tiles(K, E, H, I, n_shared, rows16):
     slots serve many tokens over long rows, else 4-row tiles (down: eight)."""
     down = _ffn_launches(8, K, E, H, I, n_shared, "bf16")[1]
     assert down[1] == (256 if rows16 else 512)
+
+
+@pytest.mark.parametrize("K,E,H,I,n_shared,dtype,tile", [
+    (1, 9, 416, 1176, 0, "bf16", False), (2, 9, 416, 1176, 0, "bf16", True), (1, 24, 1280, 1280, 1, "bf16", True),
+    (6, 23, 1096, 656, 0, "f32", False), (7, 14, 2560, 1280, 0, "f32", False), (1, 31, 888, 2296, 2, "f32", True),
+    (4, 60, 2056, 1000, 1, "f32", True), (4, 12, 4096, 1024, 0, "f32", False),
+])
+def test_batch2_kernels(K, E, H, I, n_shared, dtype, tile):
+    """Batch 2: GEMV kernels (the down launch in workgroups of four waves) or
+    4-row tiles, and both against the 64-bit oracle."""
+    from paper_2606_15453_amd import workload as W
+    down = _ffn_launches(2, K, E, H, I, n_shared, dtype)[1]
+    assert (down[1] > 256) == tile
+    cfg = W.CONFIGS["tiny" if dtype == "f32" else "qwen30b"].scaled(H=H, I=I, E=E, K=K, B=2, dtype=dtype)
+    idx, w, x = _inputs(cfg, 2, K, seed=H + I)
+    got, ref, err = _run_ffn(cfg, 1, idx, w, x, n_shared=n_shared)
+    # fp32: a few roundings of 6e-8 per chained sum of at most 80; bf16: activations rounded (2^-9 each)
+    assert np.isfinite(got).all() and err <= (1e-5 if dtype == "f32" else TOL)
