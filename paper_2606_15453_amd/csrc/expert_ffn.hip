@@ -1489,13 +1489,22 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     //   E 16 top-4 + 1 H 4096 I 1536  95.5 / 100.5   E 128 top-8 H 4096 I 1536  312 / 302
     const bool full8 = B == 8 && staged && (long long)B * (K + n_shared) * H > 8192ll * s.slots;
     s.mfma = dtype == STMOE_BF16 && (B >= kMfmaMinB || full8) && H % 64 == 0 && I % 64 == 0;
-    // A 4-row tile costs one operand load and one product per four tokens of
-    // a slot, a 16-row one the same for 1 to 16: few tokens per slot take the
-    // former (Qwen3-235B shapes at batch 16, 1.6 per slot: gate/up 332 -> 313
-    // us), shared experts (all tokens) and few experts the latter
-    // (DeepSeek-V2-Lite shapes at batch 12: FFN 130 us against 136;
-    // Mixtral shapes at batch 16: 445 against 496).
-    s.tile_up = s.mfma && n_shared == 0 && B * K <= 2 * E;
+    // Beyond batch 8, gate/up: a 4-row tile costs one operand load and one product
+    // per four tokens of a slot, a 16-row one the same for 1 to 16.  Shared
+    // experts (all tokens) and few experts take the latter (DeepSeek-V2-Lite
+    // shapes at batch 12: FFN 130 us against 136; Mixtral shapes at batch 16: 445
+    // against 496), few tokens per slot the former (Qwen3-235B shapes at batch
+    // 16, at most one: gate/up 366 -> 326 us).  Between them, us 16-row / 4-row:
+    //   staged, H a multiple of 512: up to one token per slot (E 37 top-2 H 2048
+    //     I 1152, batch 16, 37.8 / 37.0; E 8 top-1 H 2048 I 2048, batch 9, 18.8 / 19.5)
+    //   staged otherwise: up to 1.4, or H >= 2048 (E 12 top-1 H 1408 I 1152, batch
+    //     15, 16.8 / 15.5; E 18 top-2 H 1664 I 896, batch 14, 19.1 / 21.2; E 55
+    //     top-7 H 3200 I 1280, batch 13, 126 / 119)
+    //   rows of a few steps in many workgroups: never (E 132 top-5 H 640 I 1536,
+    //     batch 11, 34.5 / 39.5; E 140 top-3 H 256 I 512, batch 16, 8.9 / 9.9)
+    const bool many = staged && (H % 512 == 0 ? B * K > E : H < 2048 && 5 * B * K > 7 * E);
+    const bool brief = (staged || H == 256) && H < 1024 && I / 16 * s.slots > 1500;
+    s.tile_up = s.mfma && B >= kMfmaMinB && n_shared == 0 && B * K <= 2 * E && !many && !brief;
     s.gu_G = pick_group(H * esz / 16);
     const int cpr_i = I * esz / 16;
     s.ng = s.spg = 1;

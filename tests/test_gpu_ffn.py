@@ -296,3 +296,20 @@ def test_batch2_kernels(K, E, H, I, n_shared, dtype, tile):
     got, ref, err = _run_ffn(cfg, 1, idx, w, x, n_shared=n_shared)
     # fp32: a few roundings of 6e-8 per chained sum of at most 80; bf16: activations rounded (2^-9 each)
     assert np.isfinite(got).all() and err <= (1e-5 if dtype == "f32" else TOL)
+
+
+@pytest.mark.parametrize("B,K,E,H,I,tile", [
+    (9, 1, 8, 2048, 2048, False), (16, 2, 37, 2048, 1152, True), (14, 2, 18, 1664, 896, False), (15, 1, 12, 1408, 1152, True),
+    (11, 5, 132, 640, 1536, False), (16, 3, 140, 256, 512, False), (10, 6, 80, 2048, 64, True), (16, 2, 16, 2240, 128, True),
+])
+def test_gate_up_tiles_beyond_batch_8(B, K, E, H, I, tile):
+    """Gate/up beyond batch 8 on 4-row tiles (workgroups of 16 rows, and one
+    that publishes the plan) or on 16-row ones, and the result on both."""
+    from paper_2606_15453_amd import workload as W
+    up = _ffn_launches(B, K, E, H, I, 0, "bf16")[0]
+    assert (up[0] == -(-I // 16) * min(B * K, E) + 1) == tile
+    if H * I * E < 1 << 27:
+        cfg = W.CONFIGS["qwen30b"].scaled(H=H, I=I, E=E, K=K, B=B)
+        idx, w, x = _inputs(cfg, B, K, seed=H + I)
+        got, ref, err = _run_ffn(cfg, 1, idx, w, x)
+        assert np.isfinite(got).all() and err <= TOL
