@@ -50,8 +50,11 @@ constexpr int kMaxH = 16384;
 // batch x experts up to which the expert FFN's gate/up kernel runs the
 // gating itself (every gate/up workgroup ranks the logits, so beyond this the
 // separate router tail costs less than the larger prologue; on 4-row tiles it
-// does so earlier, see ffn_takes_plan)
+// does so earlier, see ffn_route_place)
 constexpr int kRouteInFfnMax = 128;
+// ffn_route_place: in the gate/up launch, in a tail launch, in one that also
+// makes the FFN's slot plan
+enum { kRouteInFfn, kRouteTail, kRouteTailPlan };
 
 // The batch-1 gate/up kernel computes the router's logits too where that costs
 // its workgroups less than a launch: each wave takes every fourth expert, one

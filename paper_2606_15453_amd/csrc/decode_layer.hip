@@ -24,7 +24,7 @@ int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, 
                float* y, void* ws, hipStream_t s, unsigned long long* n_experts, hipEvent_t ev_mid,
                const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router);
 bool ffn_takes_router(int B, int K, int H, int I, int E, int n_shared, int dtype);
-bool ffn_takes_plan(int B, int K, int H, int I, int E, int n_shared, int dtype);
+int ffn_route_place(int B, int K, int H, int I, int E, int n_shared, int dtype);
 int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
                    const void* const* eptr, const void* const* sptr, int n_shared, void* ws, const void* ebase,
                    size_t estride, hipStream_t st);
@@ -437,10 +437,9 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         }
     }
 
-    // R + V + P.  Without a cache: the router on the compute stream (for
-    // B*E <= 128, unless its tail makes the FFN's plan, only its logits: the
-    // FFN's gate/up kernel does softmax and top-K), then verify/update and prediction on the side stream, off the
-    // FFN's path.
+    // R + V + P.  Without a cache: the router on the compute stream (only its
+    // logits where the FFN's gate/up kernel does softmax and top-K), then
+    // verify/update and prediction on the side stream, off the FFN's path.
     // Side work still queued reads selections of this token's layers and the
     // next one's; in the usual layer order it can only collide with this
     // call from layer 0 on, so the compute stream waits for it once per token.
@@ -450,8 +449,8 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
         STMOE_HIP(hipStreamWaitEvent(c->s, c->ev_side, 0));
         c->side_pending = false;
     }
-    const bool plan = !c->cache && ffn_takes_plan(B, K, c->H, c->I, E, c->n_shared, c->dtype);
-    const bool route_in_ffn = !c->cache && !plan && B * E <= kRouteInFfnMax;
+    const int place = c->cache ? kRouteTail : ffn_route_place(B, K, c->H, c->I, E, c->n_shared, c->dtype);
+    const bool plan = place == kRouteTailPlan, route_in_ffn = place == kRouteInFfn;
     const void* ebase = c->rbase.empty() ? nullptr : c->rbase[size_t(layer)];
     const void* const* sptr = c->n_shared ? c->shared + size_t(layer) * c->n_shared : nullptr;
     float* zbuf = reinterpret_cast<float*>(c->route_ws);

@@ -210,9 +210,15 @@ def test_decode_resident_matches_oracle(name, over):
                                   dict(E=40, K=3, B=8, T=2, P=2, C=20, dtype="bf16"),
                                   dict(E=64, K=4, B=9, T=2, P=2, C=40, dtype="bf16"),
                                   dict(E=24, K=6, B=16, T=2, P=2, C=24, n_shared=2, dtype="bf16"),
-                                  dict(E=256, K=16, B=16, T=1, P=2, C=200, dtype="bf16")])
+                                  dict(E=256, K=16, B=16, T=1, P=2, C=200, dtype="bf16"),
+                                  dict(L=2, E=65, K=8, B=5, I=1024, n_shared=1, T=2, P=2, C=50),
+                                  dict(L=2, E=64, K=4, B=8, I=1088, T=2, P=2, C=40, dtype="bf16"),
+                                  dict(L=2, E=64, K=4, B=12, H=192, I=768, T=2, P=2, C=50, dtype="bf16"),
+                                  dict(L=2, E=33, K=4, B=4, H=1024, I=520, T=2, P=2, C=20),
+                                  dict(L=2, E=256, K=16, B=16, H=192, I=192, T=1, P=2, C=200, dtype="bf16")])
 def test_decode_plan_from_the_router_tail(over):
-    """Beyond B*E = 128 a resident layer's router tail also builds the FFN's
+    """Beyond B*E = 128 a resident layer's router ends in a tail launch, which
+    for many gate/up workgroups (the shapes with L = 2) also builds the FFN's
     slot plan; the capped run hands the FFN the selection instead and builds
     it there.  Both give the oracle's selections and the same bits."""
     from oracle.stmoe_oracle import MODE_STMOE
@@ -275,8 +281,8 @@ def test_decode_resident_edge_shapes(over, renorm):
         assert np.array_equal(ys_cap[t], ys[t]), t
 
 
-def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
-    """Kernel launches of one resident decode layer without a predictor."""
+def _layer_launches(B, K, E, H, I, n_shared, dtype):
+    """Launches of one resident decode layer without a predictor."""
     import torch
     from gpuhelp import DEV, graph_launches
     from paper_2606_15453_amd import stmoe as S
@@ -288,9 +294,9 @@ def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
     st = torch.cuda.Stream()
     ctx = S.DecodeContext(1, E, K, B, H, I, S.BF16 if dtype == "bf16" else S.F32, [router.data_ptr()],
                           resident_ptrs=ptrs[:E], shared_ptrs=ptrs[E:], n_shared=n_shared, stream=st)
-    n = len(graph_launches(lambda: ctx.layer(0, 0, x, y, mode=S.MODE_ON_DEMAND), st))
+    out = graph_launches(lambda: ctx.layer(0, 0, x, y, mode=S.MODE_ON_DEMAND), st)
     ctx.close()
-    return n
+    return out
 
 
 @pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,n", [
@@ -298,7 +304,7 @@ def _kernels_per_layer(B, K, E, H, I, n_shared, dtype):
     (1, 2, 8, 256, 512, 0, "f32", 2), (1, 2, 16, 256, 512, 0, "f32", 2), (1, 2, 16, 512, 512, 1, "bf16", 2),
     (1, 2, 17, 64, 256, 0, "bf16", 3), (1, 4, 64, 64, 256, 0, "f32", 3), (1, 8, 128, 64, 256, 0, "bf16", 3),
     (1, 2, 8, 520, 512, 0, "f32", 3),
-    # 4-row tiles: the router's tail makes the plan beyond four tokens or 4096 workgroups
+    # 4-row tiles: a tail launch beyond four tokens or 4096 workgroups
     (4, 2, 16, 256, 512, 0, "bf16", 3), (5, 2, 16, 256, 512, 0, "bf16", 4), (8, 4, 16, 256, 64, 0, "bf16", 4),
     (4, 4, 16, 2048, 1024, 0, "bf16", 3), (4, 4, 16, 2048, 1032, 0, "bf16", 4),
     # 16-row tiles up to B * E = 128 route in their gate/up launch (and sum partial results in one more)
@@ -309,7 +315,20 @@ def test_layer_launches(B, K, E, H, I, n_shared, dtype, n):
     of the two FFN launches where all of it runs inside the first; the logits
     alone; or logits and the tail that selects (16-row tiles sum partial
     results in a launch more)."""
-    assert _kernels_per_layer(B, K, E, H, I, n_shared, dtype) == n
+    assert len(_layer_launches(B, K, E, H, I, n_shared, dtype)) == n
+
+
+@pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,plan", [
+    (6, 8, 32, 256, 680, 0, "bf16", False), (6, 8, 32, 256, 1032, 0, "bf16", True),        # 32 slots: 1376 and 2080 workgroups
+    (5, 2, 16, 256, 512, 0, "bf16", False), (4, 4, 33, 1024, 512, 0, "f32", False), (4, 4, 33, 1024, 520, 0, "f32", True),
+    (12, 4, 64, 192, 640, 0, "bf16", False), (12, 4, 64, 192, 704, 0, "bf16", True),
+    (12, 4, 64, 512, 704, 1, "bf16", False),                                              # 16-row gate/up
+])
+def test_tail_makes_the_plan(B, K, E, H, I, n_shared, dtype, plan):
+    """The tail launch: a wave per row, or one workgroup that also makes the
+    slot plan, from 2048 workgroups of 4-row gate/up tiles on."""
+    tail = _layer_launches(B, K, E, H, I, n_shared, dtype)[1]
+    assert tail == ((1, 1024) if plan else (B, 64))
 
 
 @pytest.mark.parametrize("name,over,mode", [("tiny", dict(T=8), 2), ("tiny", dict(T=8), 3),
