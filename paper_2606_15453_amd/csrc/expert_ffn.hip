@@ -1558,20 +1558,19 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
                      (B == 2 && few2);
     s.tile = B >= 2 && !s.mfma && !few && (dtype == STMOE_F32 || act16);
     // Split the columns over the waves where each wave keeps enough of them for
-    // its share of a workgroup's prologue, 14 steps a row (DeepSeek-V2-Lite
-    // shapes at batch 4: 43.2 us split, 47.6 not; E 12 top-3 H 1920 I 1664, batch
-    // 4: 23.1 and 25.6), or, down to two steps a wave, where the launch has few
-    // workgroups otherwise (E 18 top-5 + 2 H 1536 I 512, batch 8: 16.5 and 18.2).
-    // Not for short rows in many of them (batch 8: E 32 top-8 H 1024 I 1024 32.5
-    // split, 22.2 not; E 43 top-4 H 1024 I 1920 52.2 and 35.8; E 68 top-8 + 2
-    // H 1280 I 2176 108.5 and 74.8; batch 3, E 16 top-6 + 1 H 1664 I 4096 63.6
-    // and 52.5).
+    // its share of a workgroup's prologue, 12 steps a row (DeepSeek-V2-Lite
+    // shapes at batch 4: 43.2 us split, 47.6 not; 4 layers of E 96 top-6 + 1
+    // H 1536 I 1152 at batch 7 328 and 347), or, down to two steps a wave, where
+    // the launch has few workgroups otherwise (E 28 top-7 H 896 I 384 fp32, batch
+    // 4: 14.8 and 16.7).  Not for short rows in many of them (batch 8: E 32 top-8
+    // H 1024 I 1024 32.5 split, 22.2 not; E 43 top-4 H 1024 I 1920 52.2 and 35.8;
+    // E 68 top-8 + 2 H 1280 I 2176 108.5 and 74.8).
     // With four token groups a split tile's share is not worth its prologue
     // (gate/up + down: Qwen3-30B shapes, batch 16, 134 us split with the plan
     // ready, 163 without, 127 not split; Qwen3-235B shapes 460, 496, 466).  The
     // rule must not ask for the plan: the same layer runs with and without one
     // (resident and cached) and gives the same bits.
-    s.up_split = B <= 8 && (H * esz >= 14 * 256 ||
+    s.up_split = B <= 8 && (H * esz >= 12 * 256 ||
                             (H * esz >= 2 * kWaves * 256 && (I + 15) / 16 * s.slots <= kUpSplitMaxBlocks));
     const int up_rows = s.up_split ? 4 : 4 * kWaves;
     s.up_blocks = (I + up_rows - 1) / up_rows;
