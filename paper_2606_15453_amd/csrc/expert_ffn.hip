@@ -1473,6 +1473,18 @@ constexpr bool kMfmaDownLds = true;     // MFMA down stages W_down rows through 
 template <bool BF>
 int act_bf16(const Shape& s, int B) { return BF && (s.dn_kind == 1 ? B <= 2 : s.dn_R < 4); }
 
+// The 4-row down launch: rows of its busiest CU, in eighths, with two row quads
+// per wave or with one.  Two share each activation load (Qwen3-30B shapes at
+// batch 8: 29.1 us against 34.9), one gives twice the workgroups (H 1024 fp32,
+// batch 8: 15.9 against 23.1).  One workgroup of the former fills a CU, and a
+// row costs about 9/8 in the latter.
+int down_tile_rows2(int H) { return (H / 8 + 255) / 256 * 8 * 8; }
+int down_tile_rows1(int H) { return (H / 4 + 255) / 256 * 4 * 9; }
+int down_tile_cu_rows8(int H) {
+    const int two = down_tile_rows2(H), one = down_tile_rows1(H);
+    return two <= one ? two : one;
+}
+
 Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     Shape s{};
     const int esz = dtype == STMOE_BF16 ? 2 : 4;
@@ -1480,14 +1492,25 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // The 16-row gate/up kernels that stage rows through LDS; the others keep
     // too few bytes in flight to match the 4-row tiles.
     const bool staged = H % 512 == 0 || (H % 128 == 0 && (H % 256 != 0 || I / 64 * s.slots >= kMfmaSplitKBelow));
-    // Batch 8 takes the 16-row tiles where slots serve many tokens over long
-    // rows: tokens per slot times H beyond 8192.  us per call, 16-row / 4-row:
-    //   E  8 top-4 H 4096 I  1024   38.2 /  43.4   E  8 top-2 H 4096 I 14336  444 / 417
-    //   E  8 top-8 H 4096 I  1024   39.5 /  52.5   E  8 top-4 H 2048 I  2048  45.3 / 45.6 (layer 59.5 / 55.1)
+    // Batch 8 takes the 16-row tiles where slots serve many tokens: a 4-row step
+    // costs a slot's tokens, so the line is at tokens per slot times the rows of
+    // the down launch's busiest CU (256 times them, H where it fills the chip).
+    // us per call, 16-row / 4-row (in brackets: a layer):
+    //   E  8 top-4 H 4096 I  1024   38.2 /  43.4   E  8 top-2 H 4096 I 14336   444 / 417
     //   E  8 top-4 H 4096 I 14336  439.5 / 478.4   E 64 top-6 + 2 H 2048 I 1408  110.6 / 110.0
-    //   E  8 top-8 H 4096 I 14336  454.6 / 648.3   E  8 top-8 H 1024 I  4096  61.3 / 58.7
-    //   E 16 top-4 + 1 H 4096 I 1536  95.5 / 100.5   E 128 top-8 H 4096 I 1536  312 / 302
-    const bool full8 = B == 8 && staged && (long long)B * (K + n_shared) * H > 8192ll * s.slots;
+    //   E  8 top-8 H 4096 I 14336  454.6 / 648.3   E 128 top-8 H 4096 I 1536   312 / 302
+    //   E 16 top-4 + 1 H 4096 I 1536  95.5 / 100.5   E  8 top-4 H 2048 I  2048  45.3 / 45.6 (59.5 / 55.1)
+    //   E 16 top-6 H 2176 I 2176    83.3 /  95.8   E 11 top-3 H 3968 I  7168   400 / 311
+    //   E 16 top-6 H 1536 I 3072    76.8 /  92.1   E 32 top-6 H 1664 I  3328  163.2 / 157.6 (190 / 153)
+    //   E 16 top-8 H 1664 I 1664    52.5 /  63.7   E  8 top-6 H 1024 I  4096  59.9 / 55.8
+    // And short outputs of many slots, whose 4-row down launch leaves CUs idle
+    // while the 16-row one splits the slots over workgroups: E 97 top-8 H 256
+    // I 768 28.3 / 31.7, E 64 top-8 H 384 I 1024 31.5 / 36.3, but E 64 top-8
+    // H 512 I 1024 42.0 / 38.8, E 128 top-8 H 256 I 512 23.1 / 23.4 (36.9 / 35.6).
+    const bool full8 = B == 8 &&
+        ((H > 1024 && staged &&
+          (long long)B * (K + n_shared) * down_tile_cu_rows8(H) * 32 > (H < 2048 ? 6100ll : 9300ll) * s.slots) ||
+         (H % 128 == 0 && H <= 384 && s.slots * ((I + 127) / 128) > H));
     s.mfma = dtype == STMOE_BF16 && (B >= kMfmaMinB || full8) && H % 64 == 0 && I % 64 == 0;
     // Beyond batch 8, gate/up: a 4-row tile costs one operand load and one product
     // per four tokens of a slot, a 16-row one the same for 1 to 16.  Shared
@@ -1729,12 +1752,7 @@ void launch_down_tile_r(const FfnArgs& a, hipStream_t st) {
 
 template <bool BF, int TG>
 void launch_down_tile(const FfnArgs& a, hipStream_t st) {
-    // Two row quads per wave share each activation load (Qwen3-30B shapes at
-    // batch 8: 29.1 us against 34.9), one gives twice the workgroups (H 1024
-    // fp32, batch 8: 15.9 against 23.1).  One workgroup of the former fills a
-    // CU: compare the rows of the busiest CU, a row at about 9/8 in the latter.
-    const int rows2 = (a.H / 8 + 255) / 256 * 8, rows1 = (a.H / 4 + 255) / 256 * 4;
-    if (8 * rows2 <= 9 * rows1) {
+    if (down_tile_rows2(a.H) <= down_tile_rows1(a.H)) {
         launch_down_tile_r<BF, 2, TG, 8>(a, st);
         return;
     }
