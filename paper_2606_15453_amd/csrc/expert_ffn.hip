@@ -1454,8 +1454,7 @@ struct Shape {
 };
 
 constexpr int kUpSplitMaxBlocks = 640;        // 4-row gate/up: short rows are split up to this many workgroups unsplit
-constexpr int kRouteTileMaxB = 4;             // 4-row gate/up routes itself up to this batch (ffn_route_place)
-constexpr int kRoutePlanBlocks = 2048;        // 4-row gate/up workgroups beyond which the plan comes first
+constexpr int kRoutePlanBlocks = 2048;        // 4-row gate/up workgroups beyond which the plan comes first (ffn_route_place)
 constexpr int kDownRowsWgTarget = 1024;  // lane-group down: fewest workgroups more rows per group may leave
 constexpr int kDownWgR = 4;   // rows per workgroup (whole-workgroup down)
 constexpr int kDownForceG = 0;  // lanes per down row (0: by row length)
@@ -1888,15 +1887,22 @@ FfnArgs ffn_args(const void* x, const int32_t* idx, const float* w, int B, int K
 
 // Where a resident layer's router ends.  Small routers (B*E <= kRouteInFfnMax)
 // in the gate/up launch, a launch less; but on 4-row tiles each workgroup then
-// routes ahead of four rows' weights, which pays up to four tokens (a row per
-// wave) and a few rounds of workgroups.  Else in a tail launch, which for 4-row
-// tiles of more than two rounds of workgroups also makes the plan: in fewer, a
-// workgroup's own search for its slot costs less than the plan in one workgroup
-// ahead of all.  us a token of 4 layers, in the gate/up launch / tail and plan:
+// routes ahead of four rows' weights, which pays in a few rounds of workgroups
+// with up to four tokens (a row per wave), in one round with up to eight.  Else
+// in a tail launch, which for 4-row tiles of more than two rounds of workgroups
+// also makes the plan: in fewer, a workgroup's own search for its slot costs
+// less than the plan in one workgroup ahead of all.  us a token of 4 layers, in
+// the gate/up launch / tail and plan:
 //   E 16 top-2 H 1024 I 1024, batch 4   98 / 102   E  8 top-2 H 1024 I 4096, batch 8    276 /  200
 //   E 33 top-2 H 1728 I  512, batch 3   86 /  95   E 16 top-4 H 2048 I 2048, batch 8    374 /  299
 //   E 40 top-4 H 3072 I 1024, batch 3  199 / 203   E 30 top-4 + 2 H 2048 I 1408, batch 4  259 / 243
 //   E 16 top-4 H  512 I  512, batch 4   82 /  90   E  8 top-2 H 4096 I 14336, batch 8  1557 / 1454
+// us a layer, in the gate/up launch / tail alone, as tokens (as layer calls, which
+// wait for the host's launches, or for the side stream's update behind the FFN):
+//   E 13 top-2 + 2 H 360 I 520, batch 8   23.2 / 23.6  (38.2 / 41.1)
+//   E 16 top-4 H 1024 I 1024, batch 8     34.6 / 34.9  (40.6 / 39.6)
+//   E 16 top-2 H 1024 I 512, batch 7      27.2 / 23.8  (37.4 / 41.1; 1792 workgroups)
+//   E  8 top-2 + 1 H 704 I 512 fp32, batch 16  40.4 / 38.7  (46.4 / 40.3)
 // us a layer, tail alone / tail and plan (workgroups of the gate/up launch):
 //   E 112 top-6 H 384 I 64, batch 3        18.9 / 21.3 (72)     E 17 top-4 H 1536 I 1920, batch 9  67.9 / 68.2 (2040)
 //   E 41 top-3 + 2 H 256 I 256, batch 4    21.5 / 22.1 (224)    E 48 top-2 H 1024 I 1792 fp32, batch 12  104.0 / 103.1 (2688)
@@ -1905,10 +1911,9 @@ int ffn_route_place(int B, int K, int H, int I, int E, int n_shared, int dtype) 
     const Shape s = plan_shape(B, K, H, I, E, n_shared, dtype);
     const bool small = B * E <= kRouteInFfnMax;
     if (!s.tile_up && !s.tile) return small ? kRouteInFfn : kRouteTail;
-    const bool here = small && B <= kRouteTileMaxB;
     const int blocks = s.up_blocks * s.slots;
-    if (blocks > (here ? 2 : 1) * kRoutePlanBlocks) return kRouteTailPlan;
-    return here ? kRouteInFfn : kRouteTail;
+    if (small && blocks <= (B <= 4 ? 2 * kRoutePlanBlocks : B <= 8 ? kRoutePlanBlocks / 2 : 0)) return kRouteInFfn;
+    return blocks > kRoutePlanBlocks ? kRouteTailPlan : kRouteTail;
 }
 
 // Whether the gate/up launch of these shapes can run the whole router: batch

@@ -304,8 +304,9 @@ def _layer_launches(B, K, E, H, I, n_shared, dtype):
     (1, 2, 8, 256, 512, 0, "f32", 2), (1, 2, 16, 256, 512, 0, "f32", 2), (1, 2, 16, 512, 512, 1, "bf16", 2),
     (1, 2, 17, 64, 256, 0, "bf16", 3), (1, 4, 64, 64, 256, 0, "f32", 3), (1, 8, 128, 64, 256, 0, "bf16", 3),
     (1, 2, 8, 520, 512, 0, "f32", 3),
-    # 4-row tiles: a tail launch beyond four tokens or 4096 workgroups
-    (4, 2, 16, 256, 512, 0, "bf16", 3), (5, 2, 16, 256, 512, 0, "bf16", 4), (8, 4, 16, 256, 64, 0, "bf16", 4),
+    # 4-row tiles: a tail launch beyond 4096 workgroups, from five tokens on beyond 1024, from nine on always
+    (4, 2, 16, 256, 512, 0, "bf16", 3), (5, 2, 16, 256, 512, 0, "bf16", 3), (8, 4, 16, 256, 64, 0, "bf16", 3),
+    (8, 4, 16, 256, 1024, 0, "bf16", 3), (8, 4, 16, 256, 1088, 0, "bf16", 4), (9, 4, 8, 256, 64, 0, "f32", 4),
     (4, 4, 16, 2048, 1024, 0, "bf16", 3), (4, 4, 16, 2048, 1032, 0, "bf16", 4),
     # 16-row tiles up to B * E = 128 route in their gate/up launch (and sum partial results in one more)
     (9, 4, 8, 256, 64, 0, "bf16", 4),
@@ -320,7 +321,7 @@ def test_layer_launches(B, K, E, H, I, n_shared, dtype, n):
 
 @pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,plan", [
     (6, 8, 32, 256, 680, 0, "bf16", False), (6, 8, 32, 256, 1032, 0, "bf16", True),        # 32 slots: 1376 and 2080 workgroups
-    (5, 2, 16, 256, 512, 0, "bf16", False), (4, 4, 33, 1024, 512, 0, "f32", False), (4, 4, 33, 1024, 520, 0, "f32", True),
+    (5, 5, 16, 256, 1048, 0, "bf16", False), (4, 4, 33, 1024, 512, 0, "f32", False), (4, 4, 33, 1024, 520, 0, "f32", True),
     (12, 4, 64, 192, 640, 0, "bf16", False), (12, 4, 64, 192, 704, 0, "bf16", True),
     (12, 4, 64, 512, 704, 1, "bf16", False),                                              # 16-row gate/up
 ])
