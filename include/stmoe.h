@@ -201,9 +201,10 @@ int moe_pack_expert(const void* w_gate, const void* w_up, const void* w_down, in
  *                256-byte aligned (activations and partial sums; no initial
  *                contents required); calls sharing it must be ordered on one
  *                stream
- *   B 1, bf16 shapes whose activations are held in fp32 and some small shapes
- *   run GEMV kernels, B 2 to 8 (and fp32 or ragged sizes beyond) 4-row MFMA
- *   tiles, larger B 16-row MFMA tiles; on the tiles the SwiGLU activation of
+ *   B 1, bf16 shapes whose activations are held in fp32 (long down rows at H
+ *   >= 4096) and some small shapes of B 2 to 4 run GEMV kernels, B 2 to 8 (and
+ *   fp32 or ragged sizes beyond) 4-row MFMA tiles, larger B and B 8 with many
+ *   tokens per expert 16-row MFMA tiles; on the tiles the SwiGLU activation of
  *   bf16 weights passes through bf16.
  * ---------------------------------------------------------------------- */
 size_t moe_expert_ffn_workspace_bytes(int B, int K, int E, int H, int I, int n_shared, int dtype);

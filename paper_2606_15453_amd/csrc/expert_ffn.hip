@@ -19,26 +19,28 @@
 //            the L2 of every XCD), and the summation order depends only on the
 //            routing, never on where the blobs live.
 //
-// Batch 1, bf16 shapes whose activations are held in fp32, and some small
-// shapes of batch 2 to 4 (plan_shape): GEMV kernels.
+// Batch 1, bf16 shapes whose activations are held in fp32 (H >= 4096 with long
+// down rows, batch 2 to 7 and ragged sizes beyond), and some small shapes of
+// batch 2 to 4 (plan_shape): GEMV kernels.
 // A group of G lanes (64, 32 or 16, by row length) owns R rows and strides
 // over their 16-byte chunks; the activations come from L1/L2; DPP / shuffle
 // segment sums reduce.  For long down rows the whole workgroup strides one
 // row block (split-K over its four waves).
 // Batch 2 to 8, and fp32 weights or ragged sizes beyond: 4-row tiles on the
 // 16-block 4x4 MFMA (ffn_tile.h): a step costs a slot's own tokens.
-// Batch > 8, and 8 where slots serve many tokens: 16-row tiles (v_mfma_f32_16x16x32_bf16).  The tokens form the
-// 16-row A operand (padded with zeros), 16 weight rows the B operand.  In
-// each 64-element step lane (n, q) loads elements 8q..8q+7 and 32+8q..32+8q+7
-// of row n, so every load instruction reads 16 full 64-byte row segments.
+// Batch > 8, and 8 where slots serve many tokens: 16-row tiles
+// (v_mfma_f32_16x16x32_bf16).  The tokens form the 16-row A operand (padded with
+// zeros), 16 weight rows the B operand.  In each 64-element step lane (n, q)
+// loads elements 8q..8q+7 and 32+8q..32+8q+7 of row n, so every load instruction
+// reads 16 full 64-byte row segments.
 // With few tokens per slot the gate/up phase takes 4-row tiles.
 // On both tile paths the SwiGLU activation of bf16 weights goes through bf16.
 //
 // The slot plan (distinct selected experts ascending, token masks) is built
-// on the device.  The router's tail launch of the decode path makes it where
-// it runs (ffn_route_plan): a gate/up workgroup then reads one record, where
-// building the plan in LDS costs each round of workgroups about 2 us
-// (Qwen3-30B shapes at batch 8: 3072 workgroups in four rounds).  Otherwise
+// on the device.  In the decode path the router's tail launch makes it for
+// gate/up launches of many 4-row workgroups (ffn_route_place, ffn_route_plan): a
+// workgroup then reads one record, where finding its slot costs each round of
+// workgroups about 2 us (Qwen3-30B shapes at batch 8).  Otherwise
 // every 4-row gate/up workgroup rebuilds it from topk_idx/topk_w, with no host
 // round trip or planning launch, and one that does nothing else leaves it to
 // the down launch; the GEMV and the 16-row kernels rebuild it in both.
@@ -63,7 +65,6 @@ constexpr int kMaxSlots = kMaxE + kMaxShared;
 constexpr int kDownWgTarget = 256;    // workgroups the MFMA down phase aims for
 constexpr int kMfmaMinB = 9;          // batch from which the 16-row MFMA kernels run (batch 8: plan_shape)
 constexpr int kUpInFlight = 2;        // 16-byte chunks per row in flight per lane (GEMV gate/up)
-constexpr bool kUpB1 = true;           // batch 1: the gate/up kernel that finds its slot in registers
 constexpr int kShortRowChunks = 4;    // down rows with at most this many chunks per lane are short: ...
 constexpr int kDownInFlightShort = 4; // ... the lane-group down kernel loads a slot's chunks in one step
 constexpr bool kStageX = true;        // GEMV gate/up: token activations staged in LDS ...
@@ -318,7 +319,7 @@ __device__ __forceinline__ void store_act(void* act, int act16, size_t i, float 
 }
 
 // ============================================================================
-// GEMV path (batch < 8)
+// GEMV path
 // ============================================================================
 
 // XL: the B token rows of x are staged in LDS (dynamic shared memory of
@@ -741,9 +742,9 @@ __device__ __forceinline__ void down_slot(const char* wd, size_t rowb, int cpr, 
 // together: one wait per token instead of one per chunk (an activation load
 // waits for every load issued before it).  Every accumulator still adds its
 // chunks in ascending order, so the order of the token loop does not change a
-// sum.  Lane-group kernel, DeepSeek-V2-Lite shapes at batch 4: 30.6 -> 29.2 us
-// per launch; the whole-workgroup kernel (Mixtral shapes) keeps the per-chunk
-// loads, about 1% faster there.
+// sum.  The lane-group kernel takes it (E 64 top-6 + 2 H 2048 I 1408 at batch 4,
+// a shape now on 4-row tiles: 30.6 -> 29.2 us per launch); the whole-workgroup
+// kernel keeps the per-chunk loads, about 1% faster at H 4096 I 14336.
 template <bool BF, int R, int NB, int U, bool CARRY, bool TOKENS = false>
 __device__ __forceinline__ void down_slot16(const char* wd, size_t rowb, int cpr, int c0, int S,
                                             const char* act, unsigned tm, float (&acc)[R][NB]) {
@@ -1634,20 +1635,13 @@ int launch_gate_up_r(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const int bps = (a.I + rows - 1) / rows;
     const size_t xbytes = size_t(a.B) * a.H * (BF ? 2 : 4);
     const int act16 = act_bf16<BF>(s, a.B);
-    if constexpr (kUpB1 && NB == 1) {
-        if (a.B == 1) {
-            hipLaunchKernelGGL((ffn_gate_up_b1<BF, G, R>), dim3(unsigned(bps * s.slots)), dim3(kThreads), 0, st, a,
-                               bps, act16);
-            STMOE_LAUNCHED();
-            return STMOE_OK;
-        }
-    }
-    if (kStageX && xbytes <= size_t(kXStageMax))
-        hipLaunchKernelGGL((ffn_gate_up<BF, G, R, NB, true>), dim3(unsigned(bps * s.slots)), dim3(kThreads),
-                           unsigned(xbytes), st, a, bps, act16);
+    const dim3 grid(unsigned(bps * s.slots));
+    if constexpr (NB == 1)
+        hipLaunchKernelGGL((ffn_gate_up_b1<BF, G, R>), grid, dim3(kThreads), 0, st, a, bps, act16);
+    else if (kStageX && xbytes <= size_t(kXStageMax))
+        hipLaunchKernelGGL((ffn_gate_up<BF, G, R, NB, true>), grid, dim3(kThreads), unsigned(xbytes), st, a, bps, act16);
     else
-        hipLaunchKernelGGL((ffn_gate_up<BF, G, R, NB, false>), dim3(unsigned(bps * s.slots)), dim3(kThreads), 0,
-                           st, a, bps, act16);
+        hipLaunchKernelGGL((ffn_gate_up<BF, G, R, NB, false>), grid, dim3(kThreads), 0, st, a, bps, act16);
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
@@ -1661,44 +1655,56 @@ int launch_gate_up(const FfnArgs& a, const Shape& s, hipStream_t st) {
     else return launch_gate_up_r<BF, G, NB, 1>(a, s, st);
 }
 
+// The rows per group that plan_shape leaves to the GEMV kernels: all for one
+// token; else bf16 one at batch 2 (few) or four (fp32 activations), fp32 one up
+// to batch 4, and two and four at batch 2 (few2).
 template <bool BF, int NB, int U>
-void launch_down_rows_u(const FfnArgs& a, const Shape& s, hipStream_t st) {
+int launch_down_rows_u(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const dim3 grid(unsigned(s.n_rb));
-    if constexpr (NB > 4) {      // four rows per group, or the shape takes 4-row tiles
-        hipLaunchKernelGGL((ffn_down_rows<BF, 64, 4, NB, U>), grid, dim3(kThreads), 0, st, a);
-        return;
+    if constexpr (NB <= 2 || (!BF && NB == 4)) {
+        if (s.dn_R == 1) {
+            if (s.dn_G == 16)
+                hipLaunchKernelGGL((ffn_down_rows<BF, 16, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
+            else if (s.dn_G == 32)
+                hipLaunchKernelGGL((ffn_down_rows<BF, 32, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
+            else
+                hipLaunchKernelGGL((ffn_down_rows<BF, 64, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
+            return STMOE_OK;
+        }
     }
-    if (s.dn_G == 16)
-        hipLaunchKernelGGL((ffn_down_rows<BF, 16, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
-    else if (s.dn_G == 32 && s.dn_R == 2)
-        hipLaunchKernelGGL((ffn_down_rows<BF, 32, 2, NB, U>), grid, dim3(kThreads), 0, st, a);
-    else if (s.dn_G == 32)
-        hipLaunchKernelGGL((ffn_down_rows<BF, 32, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
-    else if (s.dn_R == 4)
-        hipLaunchKernelGGL((ffn_down_rows<BF, 64, 4, NB, U>), grid, dim3(kThreads), 0, st, a);
-    else if (s.dn_R == 2)
-        hipLaunchKernelGGL((ffn_down_rows<BF, 64, 2, NB, U>), grid, dim3(kThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL((ffn_down_rows<BF, 64, 1, NB, U>), grid, dim3(kThreads), 0, st, a);
+    if constexpr (NB == 1 || (!BF && NB == 2)) {
+        if (s.dn_R == 2) {
+            if (s.dn_G == 32)
+                hipLaunchKernelGGL((ffn_down_rows<BF, 32, 2, NB, U>), grid, dim3(kThreads), 0, st, a);
+            else
+                hipLaunchKernelGGL((ffn_down_rows<BF, 64, 2, NB, U>), grid, dim3(kThreads), 0, st, a);
+            return STMOE_OK;
+        }
+    }
+    if constexpr (BF || NB <= 2) {
+        if (s.dn_R == 4) {
+            hipLaunchKernelGGL((ffn_down_rows<BF, 64, 4, NB, U>), grid, dim3(kThreads), 0, st, a);
+            return STMOE_OK;
+        }
+    }
+    set_error("ffn_down_rows: no kernel for these rows per group");
+    return STMOE_EINVAL;
 }
 
 // short rows (at most kShortRowChunks chunks per lane) load a slot's chunks in one step
 template <bool BF, int NB>
-void launch_down_rows(const FfnArgs& a, const Shape& s, hipStream_t st) {
+int launch_down_rows(const FfnArgs& a, const Shape& s, hipStream_t st) {
     if ((a.I * (BF ? 2 : 4) / 16 + s.dn_G - 1) / s.dn_G <= kShortRowChunks)
-        launch_down_rows_u<BF, NB, kDownInFlightShort>(a, s, st);
-    else
-        launch_down_rows_u<BF, NB, 2>(a, s, st);
+        return launch_down_rows_u<BF, NB, kDownInFlightShort>(a, s, st);
+    return launch_down_rows_u<BF, NB, 2>(a, s, st);
 }
 
 template <bool BF, int NB>
 int launch_down(const FfnArgs& a, const Shape& s, hipStream_t st) {
-    const dim3 grid(unsigned(s.n_rb));
-    if (s.dn_kind == 1) {
-        hipLaunchKernelGGL((ffn_down_wg<BF, kDownWgR, NB>), grid, dim3(kThreads), 0, st, a);
-    } else {
-        launch_down_rows<BF, NB>(a, s, st);
-    }
+    if (s.dn_kind == 1)
+        hipLaunchKernelGGL((ffn_down_wg<BF, kDownWgR, NB>), dim3(unsigned(s.n_rb)), dim3(kThreads), 0, st, a);
+    else if (int rc = launch_down_rows<BF, NB>(a, s, st))
+        return rc;
     STMOE_LAUNCHED();
     return STMOE_OK;
 }
