@@ -53,7 +53,7 @@
 // Workspace of moe_expert_ffn_noalloc: one copy per GPU, held until the
 // process ends.  In host code this name is a stand-in, not a device address;
 // the device address comes from hipGetSymbolAddress (see noalloc_scratch).
-static __device__ __align__(256) unsigned char scratch[(size_t(16) << 20) + (size_t(32) << 10)];
+static __device__ __align__(256) unsigned char scratch[(size_t(18) << 20) + (size_t(32) << 10)];
 
 namespace stmoe {
 namespace {
@@ -1613,7 +1613,6 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
 }
 
 constexpr size_t kSlotListBytes = (sizeof(SlotList) + 255) / 256 * 256;
-static_assert(kSlotListBytes <= sizeof(scratch) - (size_t(16) << 20), "scratch too small");
 
 struct WsLayout {
     size_t act, part, slots, total;
@@ -2015,8 +2014,14 @@ extern "C" int moe_expert_ffn(const void* x, const int32_t* topk_idx, const floa
 
 namespace {
 
-// 16 MiB of activations and partial sums, and the slot plan behind them
+// 16 MiB of activations and partial sums, and the slot plan behind them.  At
+// batch 8 partial sums (16-row tiles, where plan_shape takes them) lie in 2 MiB
+// more, so that which tiles a shape takes does not decide whether it fits: at
+// most 32768 / H + 1 slot groups of 8 rows of H floats.
 constexpr size_t kNoAllocScratchBytes = (size_t(16) << 20) + kSlotListBytes;
+constexpr size_t kNoAllocPartBytes = size_t(2) << 20;
+static_assert(size_t(kMaxH + 32768) * 8 * sizeof(float) <= kNoAllocPartBytes, "scratch too small");
+static_assert(kNoAllocScratchBytes + kNoAllocPartBytes <= sizeof(scratch), "scratch too small");
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices];      // device address of `scratch` per device (null until resolved)
@@ -2053,7 +2058,8 @@ extern "C" int moe_expert_ffn_noalloc(const void* x, const int32_t* topk_idx, co
     STMOE_CHECK(n_shared >= 0 && n_shared <= kMaxShared, "n_shared must be in [0, 8]");
     STMOE_CHECK(n_shared == 0 || shared_ptrs, "shared_ptrs is required when n_shared > 0");
     STMOE_CHECK(dtype == STMOE_BF16 || dtype == STMOE_F32, "dtype must be STMOE_BF16 or STMOE_F32");
-    const size_t need = moe_expert_ffn_workspace_bytes(B, K, E, H, I, n_shared, dtype);
+    const WsLayout L = ws_layout(B, H, I, plan_shape(B, K, H, I, E, n_shared, dtype));
+    const size_t need = B == 8 ? L.total - (L.slots - L.part) : L.total;
     if (need > kNoAllocScratchBytes) {
         set_error("moe_expert_ffn_noalloc: this shape needs " + std::to_string(need) +
                   " bytes of workspace; the library's scratch holds " + std::to_string(kNoAllocScratchBytes) +

@@ -70,3 +70,29 @@ def test_noalloc_refuses_beyond_scratch():
                                        S.BF16, dummy.data_ptr(), None, 0, dummy.data_ptr(), None)
     assert rc == S.ENOMEM
     assert "scratch" in S._lib.stmoe_last_error().decode()
+
+
+def test_noalloc_takes_batch_8_up_to_16_mib_of_activations():
+    """16 MiB of activations at batch 8 on 16-row tiles, whose partial sums
+    come on top: accepted, with the workspace entry's bits."""
+    import torch
+    from gpuhelp import DEV
+    from paper_2606_15453_amd import stmoe as S
+    B, K, E, H, I = 8, 16, 32, 1152, 16384
+    act = min(B * K, E) * B * I * 4
+    assert act == 16 << 20
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    blob = torch.empty(3 * H * I, dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g)
+    x = torch.randn((B, H), generator=g, device=DEV).to(torch.bfloat16)
+    idx = torch.stack([torch.arange(b, b + K, device=DEV) % E for b in range(B)]).to(torch.int32)
+    w = torch.rand((B, K), generator=g, device=DEV)
+    table = torch.tensor([blob.data_ptr()] * E, dtype=torch.int64, device=DEV)
+    nbytes = S.ffn_workspace_bytes(B, K, E, H, I, 0, S.BF16)
+    assert nbytes > act + (64 << 10)                       # partial sums
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device=DEV)
+    y, ref = (torch.full((B, H), float("nan"), device=DEV) for _ in range(2))
+    S.expert_ffn(x, idx, w, H, I, E, S.BF16, table, ref, ws)
+    S.expert_ffn_noalloc(x, idx, w, H, I, E, S.BF16, table, y)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.equal(y, ref)
