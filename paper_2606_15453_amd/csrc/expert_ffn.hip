@@ -1732,26 +1732,35 @@ int launch_gemv_b(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t e
 
 // -------------------------------------------------------------- tile kernels
 
-template <bool BF, int TG>
-void launch_up_tile(const FfnArgs& a, const Shape& s, hipStream_t st) {
+template <bool BF, int TG, bool LINES>
+void launch_up_tile_l(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const int extra = a.ready ? 0 : 1;       // the workgroup that publishes the plan
     const dim3 grid(unsigned(s.up_blocks * a.cap + extra));
     if constexpr (TG < 4) {
         if (s.up_split) {
-            hipLaunchKernelGGL((ffn_up_tile<BF, TG, true>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+            hipLaunchKernelGGL((ffn_up_tile<BF, TG, true, LINES>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
             return;
         }
     }
-    hipLaunchKernelGGL((ffn_up_tile<BF, TG, false>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+    hipLaunchKernelGGL((ffn_up_tile<BF, TG, false, LINES>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+}
+
+template <bool BF, int TG>
+void launch_up_tile(const FfnArgs& a, const Shape& s, hipStream_t st) {
+    if (a.H * (BF ? 2 : 4) % 128) launch_up_tile_l<BF, TG, false>(a, s, st);
+    else launch_up_tile_l<BF, TG, true>(a, s, st);
 }
 
 template <bool BF, int RQ, int TG, int W>
 void launch_down_tile_r(const FfnArgs& a, hipStream_t st) {
     const dim3 grid(unsigned(a.H / (4 * RQ))), block(64 * W);
-    if (a.I * (BF ? 2 : 4) % 256)
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true>), grid, block, 0, st, a);
+    const int rowb = a.I * (BF ? 2 : 4);
+    if (rowb % 128)
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true, false>), grid, block, 0, st, a);
+    else if (rowb % 256)
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true, true>), grid, block, 0, st, a);
     else
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, false, true>), grid, block, 0, st, a);
 }
 
 template <bool BF, int TG>

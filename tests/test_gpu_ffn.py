@@ -185,6 +185,8 @@ def test_ffn_repeated_and_out_of_range_entries(name, row):
     (6, 4, 60, 2056, 1000, 1, "bf16"),   # 257 pairs of row quads: one quad per down wave
     (8, 8, 128, 2048, 768, 0, "bf16"),   # the largest batch of two token groups
     (8, 8, 8, 256, 64, 0, "f32"),        # every token in every slot: both token groups full
+    (5, 3, 20, 576, 192, 1, "bf16"),     # rows of whole cache lines that end inside a 256-byte step
+    (4, 2, 12, 584, 200, 1, "f32"),      # rows that share cache lines
     (9, 1, 1, 72, 104, 0, "bf16"),       # one expert serves nine tokens: four token groups
     (14, 1, 26, 704, 2192, 0, "bf16"),   # batch beyond 8 with sizes the 16-row tiles do not take
     (16, 2, 5, 64, 8, 8, "f32"),         # the largest batch, eight shared experts
