@@ -94,23 +94,23 @@ def test_route_reports_near_ties_consistently():
 @pytest.mark.parametrize("E,K", [(8, 2), (32, 32 // 2), (33, 8), (64, 16), (65, 1), (200, 16), (256, 16)])
 @pytest.mark.parametrize("B", [1, 5])
 def test_route_ties_and_extremes(E, K, B):
-    """Rows of few distinct logits, infinities among them: the selection is
-    ordered by (logit descending, index ascending), ties that straddle the
-    K-th place included.  Logits come out exactly (H = 8, one product each)."""
+    """Rows of few distinct logits, minus infinity among them (finite factors
+    whose product overflows): the selection is ordered by (logit descending,
+    index ascending), ties that straddle the K-th place included.  Logits come
+    out exactly (H = 8, one product each)."""
     import torch
     from gpuhelp import DEV, to_dev
     from paper_2606_15453_amd import stmoe as S
     rng = np.random.default_rng(E * 31 + K + B)
-    x = np.zeros((B, 8), np.float32)
-    x[np.arange(B), np.arange(B) % 4] = 1.0
-    for levels in ([0.0], [-1.5, -1.5, 2.0], [0.0, -0.0, 1.0, -3.0], [float("-inf"), 0.25, -0.25]):
+    for levels, scale in (([0.0], 1.0), ([-1.5, -1.5, 2.0], 1.0), ([0.0, -0.0, 1.0, -3.0], 1.0),
+                          ([-3e38, 0.25, -0.25], 2.0)):
+        x = np.zeros((B, 8), np.float32)
+        x[np.arange(B), np.arange(B) % 4] = scale
         g = np.zeros((E, 8), np.float32)
         g[:, :4] = rng.choice(levels, size=(E, 4))
-        with np.errstate(invalid="ignore"):
-            z = np.stack([g[:, b % 4] for b in range(B)])
-        if np.isinf(g).any():
-            g[:, :4] = np.where(np.isinf(g[:, :4]), -3e38, g[:, :4])      # 0 * inf would be NaN
-            z = np.stack([g[:, b % 4] for b in range(B)])
+        with np.errstate(over="ignore"):
+            z = np.stack([g[:, b % 4] * np.float32(scale) for b in range(B)])
+        assert np.isneginf(z).any() == (scale == 2.0)
         idx = torch.full((B, K), -7, dtype=torch.int32, device=DEV)
         w = torch.zeros((B, K), dtype=torch.float32, device=DEV)
         ws = torch.zeros(S.route_workspace_bytes(B, E), dtype=torch.uint8, device=DEV)
