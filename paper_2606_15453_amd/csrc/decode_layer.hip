@@ -22,7 +22,8 @@ namespace stmoe {
 int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
                int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
                float* y, void* ws, hipStream_t s, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router);
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router,
+               int host);
 bool ffn_takes_router(int B, int K, int H, int I, int E, int n_shared, int dtype);
 int ffn_route_place(int B, int K, int H, int I, int E, int n_shared, int dtype);
 int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, int K, int H, int I, int E, int dtype,
@@ -561,7 +562,7 @@ int decode_layer(moe_ctx* c, int token, int layer, const void* x, float* y, int 
                             sptr, c->n_shared,
                             y, c->ffn_ws, c->s, timed ? c->n_experts : nullptr, e1,
                             route_in_ffn && !router_in_ffn ? zbuf : nullptr, c->renorm, ebase, c->rstride, plan,
-                            router_in_ffn ? c->router[layer] : nullptr))
+                            router_in_ffn ? c->router[layer] : nullptr, c->cache != nullptr))
         return rc;
     if (timed) {
         if (int rc = stamp_event(tl.down1, c->s)) return rc;

@@ -94,6 +94,7 @@ struct FfnArgs {
     unsigned long long* n_experts;   // optional: += distinct routed experts (block 0)
     SlotList* slots;          // the slot plan in global memory (null: nobody reads it)
     int ready;                       // ... built before the gate/up launch
+    int host;                        // blobs may lie in host memory
     int cap;                         // slots at most
     int act16;                       // GEMV and tile activations held in bf16
     int ng, spg;                     // expert-slot groups of the down phase, slots per group
@@ -1732,35 +1733,35 @@ int launch_gemv_b(const FfnArgs& a, const Shape& s, hipStream_t st, hipEvent_t e
 
 // -------------------------------------------------------------- tile kernels
 
-template <bool BF, int TG, bool LINES>
+template <bool BF, int TG, bool SHARED>
 void launch_up_tile_l(const FfnArgs& a, const Shape& s, hipStream_t st) {
     const int extra = a.ready ? 0 : 1;       // the workgroup that publishes the plan
     const dim3 grid(unsigned(s.up_blocks * a.cap + extra));
     if constexpr (TG < 4) {
         if (s.up_split) {
-            hipLaunchKernelGGL((ffn_up_tile<BF, TG, true, LINES>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+            hipLaunchKernelGGL((ffn_up_tile<BF, TG, true, SHARED>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
             return;
         }
     }
-    hipLaunchKernelGGL((ffn_up_tile<BF, TG, false, LINES>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
+    hipLaunchKernelGGL((ffn_up_tile<BF, TG, false, SHARED>), grid, dim3(kThreads), 0, st, a, s.up_blocks);
 }
 
 template <bool BF, int TG>
 void launch_up_tile(const FfnArgs& a, const Shape& s, hipStream_t st) {
-    if (a.H * (BF ? 2 : 4) % 128) launch_up_tile_l<BF, TG, false>(a, s, st);
-    else launch_up_tile_l<BF, TG, true>(a, s, st);
+    if (a.host && a.H * (BF ? 2 : 4) % 128) launch_up_tile_l<BF, TG, true>(a, s, st);
+    else launch_up_tile_l<BF, TG, false>(a, s, st);
 }
 
 template <bool BF, int RQ, int TG, int W>
 void launch_down_tile_r(const FfnArgs& a, hipStream_t st) {
     const dim3 grid(unsigned(a.H / (4 * RQ))), block(64 * W);
     const int rowb = a.I * (BF ? 2 : 4);
-    if (rowb % 128)
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true, false>), grid, block, 0, st, a);
-    else if (rowb % 256)
+    if (a.host && rowb % 128)
         hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true, true>), grid, block, 0, st, a);
+    else if (rowb % 256)
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, true, false>), grid, block, 0, st, a);
     else
-        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, false, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((ffn_down_tile<BF, RQ, TG, W, false, false>), grid, block, 0, st, a);
 }
 
 template <bool BF, int TG>
@@ -1967,10 +1968,12 @@ int ffn_route_plan(const float* z, int renorm, int32_t* idx, float* w, int B, in
 // idx/w are outputs, written before the down kernel reads them; `router` (where
 // ffn_takes_router says so) instead of `logits`: the same, logits included.
 // `ready`: the plan is in the workspace (ffn_route_plan on this stream).
+// `host`: expert blobs may lie in host memory (overflow of a capped cache).
 int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, int H, int I, int E,
                int dtype, const void* const* eptr, const void* const* sptr, int n_shared,
                float* y, void* ws, hipStream_t st, unsigned long long* n_experts, hipEvent_t ev_mid,
-               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router) {
+               const float* logits, int renorm, const void* ebase, size_t estride, int ready, const void* router,
+               int host) {
     if (logits && B * E > kRouteInFfnMax) {
         set_error("ffn_launch: routing inside the FFN needs B*E <= 128");
         return STMOE_EINVAL;
@@ -1982,6 +1985,7 @@ int ffn_launch(const void* x, const int32_t* idx, const float* w, int B, int K, 
     a.renorm = renorm;
     a.ready = ready;
     a.router = router;
+    a.host = host;
     if (s.mfma) return launch_mfma(a, s, st, ev_mid);
     if (s.tile) return dtype == STMOE_BF16 ? launch_tile<true>(a, s, st, ev_mid) : launch_tile<false>(a, s, st, ev_mid);
     return dtype == STMOE_BF16 ? launch_gemv_b<true>(a, s, st, ev_mid)
@@ -2018,7 +2022,7 @@ extern "C" int moe_expert_ffn(const void* x, const int32_t* topk_idx, const floa
     STMOE_CHECK((reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(ws) & 255) == 0,
                 "x must be 16-byte and ws 256-byte aligned");
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y,
-                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr);
+                      ws, as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr, 0);
 }
 
 namespace {
@@ -2079,5 +2083,5 @@ extern "C" int moe_expert_ffn_noalloc(const void* x, const int32_t* topk_idx, co
     void* ws = nullptr;
     if (int rc = noalloc_scratch(&ws)) return rc;
     return ffn_launch(x, topk_idx, topk_w, B, K, H, I, E, dtype, expert_ptrs, shared_ptrs, n_shared, y, ws,
-                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr);
+                      as_stream(stream), nullptr, nullptr, nullptr, 0, nullptr, 0, 0, nullptr, 0);
 }

@@ -221,17 +221,19 @@ __device__ __forceinline__ void selected_mask(const Sel& s, uint32_t* words, uin
     for (int q = 0; q < 8; ++q) m[q] = uint32_t(uni(int(words[q])));
 }
 
-// A weight chunk.  Weights are read once, past the caches, where rows are whole
-// 128-byte lines (LINES).  Other rows' 256-byte segments share lines with the
-// next step's: read past the caches those lines come twice, over the host link,
-// too, where overflow experts of a capped cache stay in host memory (nontemporal
-// / cached loads: a capped token of 3 layers E 10 top-4 H 1816 I 1384 fp32, batch
-// 2, 4326 / 3960 us; FFN E 60 top-4 + 1 H 2056 I 1000, batch 6, 59.7 / 50.8;
-// whole lines the other way, Qwen3-30B shapes at batch 8 352 / 390 us, 4 layers).
-template <bool LINES>
+// A weight chunk.  Weights are read once, past the caches.  Not so (SHARED)
+// behind a capped cache, whose overflow experts stay in host memory, for rows
+// that are not whole 128-byte lines: their 256-byte segments share lines with
+// the next step's, and read past the caches those lines come over the host link
+// twice (a token of 3 layers E 10 top-4 H 1816 I 1384 fp32, batch 2: 4326 us,
+// 3960 through the caches).  In HBM such rows gain 2 to 15% a token that way, but
+// a pass over caches full of written lines lost 45% (FFN E 60 top-4 + 1 H 2056
+// I 1000, batch 6: 64 us and 100), and whole lines lose always (Qwen3-30B shapes
+// at batch 8, 4 layers: 352 and 390).
+template <bool SHARED>
 __device__ __forceinline__ uint4 ld_weight(const char* p) {
-    if constexpr (LINES) return ld_stream(p);
-    else return ld_cached(p);
+    if constexpr (SHARED) return ld_cached(p);
+    else return ld_stream(p);
 }
 
 // One wave's rows of a slot: what the stream below needs.
@@ -251,7 +253,7 @@ struct UpTile {
 // step of its own ahead of the loop.  The full steps start at `rot` and run
 // around, so that waves that start together do not all read the same column
 // of rows a power of two apart (the same memory channels).
-template <bool BF, int TG, int TGX, int U, bool SK, bool LINES>
+template <bool BF, int TG, int TGX, int U, bool SK, bool SHARED>
 __device__ __forceinline__ void up_stream(const FfnArgs& a, const UpTile& z, const int (&mytok)[TGX],
                                           const float (&myw)[TGX], float (&red)[SK ? kWaves : 1][2][TGX][16]) {
     const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), c = lane >> 2, nt = z.nt;
@@ -271,8 +273,8 @@ __device__ __forceinline__ void up_stream(const FfnArgs& a, const UpTile& z, con
         at = at + 1 == s0 + n ? s0 : at + 1;
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg) st.x[tg] = ld_cached(z.x + o + xoff[tg]);
-        st.g = ld_weight<LINES>(z.wg + o + woff);
-        st.u = ld_weight<LINES>(wu + o + woff);
+        st.g = ld_weight<SHARED>(z.wg + o + woff);
+        st.u = ld_weight<SHARED>(wu + o + woff);
     };
     const f32x4 fz = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 accg[TG], accu[TG];
@@ -292,8 +294,8 @@ __device__ __forceinline__ void up_stream(const FfnArgs& a, const UpTile& z, con
         const bool in = c < rem;
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg) st[0].x[tg] = in ? ld_cached(z.x + o + xoff[tg]) : zero;
-        st[0].g = in ? ld_weight<LINES>(z.wg + o + woff) : zero;
-        st[0].u = in ? ld_weight<LINES>(wu + o + woff) : zero;
+        st[0].g = in ? ld_weight<SHARED>(z.wg + o + woff) : zero;
+        st[0].u = in ? ld_weight<SHARED>(wu + o + woff) : zero;
         compute(st[0]);
     }
     if (n >= U) {
@@ -372,7 +374,7 @@ constexpr int kUpTileSteps = 2;       // steps in flight per wave (gate/up)
 // workgroups pays this kernel's prologue, and one record read is the shortest.
 // Otherwise every wave finds its slot from the selection, and workgroup 0 only
 // publishes the plan (and the selection it routed).
-template <bool BF, int TG, bool SK, bool LINES>
+template <bool BF, int TG, bool SK, bool SHARED>
 __global__ __launch_bounds__(kThreads, TG == 4 ? 4 : TG == 2 ? 6 : 7) void ffn_up_tile(FfnArgs a, int bps) {
     __shared__ uint32_t words[kWaves][8];
     __shared__ int32_t s_idx[kMaxB * kMaxK];
@@ -488,8 +490,8 @@ __global__ __launch_bounds__(kThreads, TG == 4 ? 4 : TG == 2 ? 6 : 7) void ffn_u
     z.nt = nt;
     z.rot = SK ? blk : blk * kWaves + wave;
     z.act = size_t(j) * a.B * a.I + i0;
-    if (TG > 1 && z.nt > 4) up_stream<BF, TG, TG, 1, SK, LINES>(a, z, mytok, myw, red);
-    else up_stream<BF, 1, TG, kUpTileSteps, SK, LINES>(a, z, mytok, myw, red);
+    if (TG > 1 && z.nt > 4) up_stream<BF, TG, TG, 1, SK, SHARED>(a, z, mytok, myw, red);
+    else up_stream<BF, 1, TG, kUpTileSteps, SK, SHARED>(a, z, mytok, myw, red);
 }
 
 // down: one workgroup = 4 * RQ output rows; its waves split the (slot, step)
@@ -497,7 +499,7 @@ __global__ __launch_bounds__(kThreads, TG == 4 ? 4 : TG == 2 ? 6 : 7) void ffn_u
 // steps in flight per wave.
 // Workgroups start one step apart and run around the pairs (rows a power of
 // two apart read different memory channels).
-template <bool BF, int RQ, int TG, int W, bool REM, bool LINES>
+template <bool BF, int RQ, int TG, int W, bool REM, bool SHARED>
 __global__ __launch_bounds__(64 * W, (W == 16 ? 4 : TG == 4 ? 2 : TG * RQ == 4 ? 3 : 4)) void ffn_down_tile(FfnArgs a) {
     constexpr int U = W == 16 && TG == 1 ? 4 : 3;
     __shared__ SlotTable p;
@@ -541,7 +543,7 @@ __global__ __launch_bounds__(64 * W, (W == 16 ? 4 : TG == 4 ? 2 : TG * RQ == 4 ?
         }
         const uint32_t wo = uint32_t(lane & 3) * uint32_t(rowb) + uint32_t(ch) * 16u;
 #pragma unroll
-        for (int q = 0; q < RQ; ++q) st.w[q] = ld_weight<LINES>(wp + q * quad + wo);
+        for (int q = 0; q < RQ; ++q) st.w[q] = ld_weight<SHARED>(wp + q * quad + wo);
         const bool wrap = k + 1 == spr;
         k = wrap ? 0 : k + 1;
         j = wrap ? (j + 1 == n_slots ? 0 : j + 1) : j;

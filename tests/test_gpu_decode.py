@@ -236,6 +236,25 @@ def test_decode_plan_from_the_router_tail(over):
             assert np.array_equal(a[1][t][l], b[1][t][l]), (t, l)
 
 
+@pytest.mark.parametrize("over", [dict(E=12, K=4, B=5, H=264, I=520, C=6, dtype="bf16"),      # neither row whole lines
+                                  dict(E=10, K=4, B=3, H=520, I=320, C=5),                    # gate/up rows not
+                                  dict(E=16, K=6, B=6, H=256, I=1048, C=7, dtype="bf16"),     # down rows not
+                                  dict(E=12, K=4, B=12, H=264, I=72, C=4, n_shared=1)])
+def test_decode_overflow_rows_share_lines(over):
+    """Device decisions, fewer slots than a step needs: the FFN reads overflow
+    experts from host memory, rows that are not whole cache lines through the
+    caches.  The outputs are those of the resident stack bit for bit."""
+    from paper_2606_15453_amd import workload as W
+    cfg = W.CONFIGS["tiny"].scaled(L=2, T=3, P=2, **over)
+    st = Stack(cfg)
+    a = _run_gpu(st, 0, capped=False)
+    b = _run_gpu(st, 0, capped=True, device=1)
+    assert b[3]["overflow"] > 0
+    for t in range(cfg.T):
+        for l in range(cfg.L):
+            assert np.array_equal(a[1][t][l], b[1][t][l]), (t, l)
+
+
 @pytest.mark.parametrize("over,renorm", [(dict(E=7, K=3, B=2, T=6, P=3), False),
                                          (dict(E=64, K=4, B=4, T=4, P=2, C=16), False),
                                          (dict(B=3, T=6, P=3), True),
