@@ -132,6 +132,7 @@ def parse():
     return ap.parse_args()
 
 
+UP_KERNELS = ("ffn_gate_up", "ffn_up_tile")      # kernels of the FFN's gate/up phase
 COUNTERS_MD = os.path.join(ROOT, "profiles", "ffn_gate_up_mixtral8x7b_b1_counters.md")
 POOL_TIER = "host"      # set from --pool
 FFN_SOURCES = [os.path.join(ROOT, "paper_2606_15453_amd", "csrc", f)
@@ -238,16 +239,16 @@ def summarize_counters(fetch_csv, write_csv, meta_json):
     f = counter_means(fetch_csv, "FETCH_SIZE")
     w = counter_means(write_csv, "WRITE_SIZE")
 
-    def pick(d, key):
-        m = [(k, v) for k, v in d.items() if key in k]
+    def pick(d, *keys):
+        m = [(k, v) for k, v in d.items() if any(key in k for key in keys)]
         if not m:
-            raise SystemExit(f"no {key} dispatches in the counter file")
+            raise SystemExit(f"no {keys[0]} dispatches in the counter file")
         return m[0][1]
 
     cf, _ = pick(f, "calib_copy_kernel")
     cw, _ = pick(w, "calib_copy_kernel")
-    gf, n_g = pick(f, "ffn_gate_up")
-    gw, _ = pick(w, "ffn_gate_up")
+    gf, n_g = pick(f, *UP_KERNELS)
+    gw, _ = pick(w, *UP_KERNELS)
     df, _ = pick(f, "ffn_down")
     dw, _ = pick(w, "ffn_down")
     kf = CALIB_BYTES / (cf * 1024.0)
@@ -298,8 +299,8 @@ def summarize_counters(fetch_csv, write_csv, meta_json):
     print("\n".join(out))
 
 
-DECODE_KERNELS = ("route_logits_kernel", "route_tail_kernel", "route_update_predict_kernel", "ffn_gate_up",
-                  "ffn_down", "ffn_reduce", "update_predict", "decide_kernel", "blit_kernel", "set_table_kernel")
+DECODE_KERNELS = ("route_logits_kernel", "route_tail_kernel", "route_plan_kernel", "route_update_predict_kernel",
+                  *UP_KERNELS, "ffn_down", "ffn_reduce", "update_predict", "decide_kernel", "blit_kernel", "set_table_kernel")
 
 
 def summarize_gaps(trace_csv, title, cmd, skip_frac=0.25):
@@ -320,13 +321,13 @@ def summarize_gaps(trace_csv, title, cmd, skip_frac=0.25):
                  e=int(r["End_Timestamp"])) for r in rows if r.get("End_Timestamp")]
     rows.sort(key=lambda r: r["s"])
     is_dec = lambda r: r["name"].startswith(DECODE_KERNELS)
-    ffn_q = max(set(r["q"] for r in rows if r["name"].startswith("ffn_gate_up")),
+    ffn_q = max(set(r["q"] for r in rows if r["name"].startswith(UP_KERNELS)),
                 key=lambda q: sum(1 for r in rows if r["q"] == q))
     comp = [r for r in rows if r["q"] == ffn_q]
     idx = [i for i, r in enumerate(comp) if is_dec(r)]
     comp = [r for r in comp[idx[0]:idx[-1] + 1] if is_dec(r)]
     comp = comp[int(len(comp) * skip_frac):]
-    while comp and not comp[0]["name"].startswith(("route", "ffn_gate_up")):
+    while comp and not comp[0]["name"].startswith(("route", *UP_KERNELS)):
         comp = comp[1:]
     acc = {}
     for prev, cur in zip(comp, comp[1:]):
@@ -336,7 +337,7 @@ def summarize_gaps(trace_csv, title, cmd, skip_frac=0.25):
         d[2] += max(cur["s"] - prev["e"], 0) / 1e3
     span = (comp[-1]["e"] - comp[0]["e"]) / 1e3
     busy = sum((r["e"] - r["s"]) / 1e3 for r in comp[1:])
-    n_up = max(sum(1 for r in comp[1:] if r["name"].startswith("ffn_gate_up")), 1)
+    n_up = max(sum(1 for r in comp[1:] if r["name"].startswith(UP_KERNELS)), 1)
     out = [f"# {title}", "",
            "Command (run from `/tmp` with `TMPDIR=/tmp`, repository at `$R`):", "", "```", cmd,
            f"python bench.py --summarize-gaps <kernel_trace.csv> '<title>' '<command>'", "```", "",
@@ -818,7 +819,7 @@ def summarize_floor(rf_csv, fs_csv):
         for (r, kname, wgs), t in groups.items():
             if r != run or "reduce" in kname:
                 continue
-            nbytes = nb * (2 if "gate_up" in kname else 1) * cfg.H * cfg.I * esz
+            nbytes = nb * (2 if any(k in kname for k in UP_KERNELS) else 1) * cfg.H * cfg.I * esz
             med = _median_kept(t)[0]
             short = kname.replace("stmoe::", "")
             fl = f"{floor_us(nbytes):.2f} | {floor_us(nbytes) / med:.3f}" if nbytes >= pts[0][0] else "- | -"

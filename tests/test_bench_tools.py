@@ -4,6 +4,9 @@ import csv
 import io
 import contextlib
 
+
+import pytest
+
 import bench
 
 FIELDS = ["Kind", "Kernel_Name", "Start_Timestamp", "End_Timestamp", "Workgroup_Size_X", "Grid_Size_X"]
@@ -47,7 +50,8 @@ def test_summarize_policy_pivots_rows(tmp_path):
     assert lines[2] == "| w | 57 (measured) | 0.00 | 4.00 | +0.250 |"
 
 
-def test_summarize_floor_interpolates_the_read_floor(tmp_path):
+@pytest.mark.parametrize("up_kernel", ["ffn_gate_up", "ffn_up_tile"])
+def test_summarize_floor_interpolates_the_read_floor(tmp_path, up_kernel):
     from paper_2606_15453_amd import workload as W
     rf = tmp_path / "rf.csv"
     # 32 KiB per workgroup: 768 workgroups = 24 MiB in 6 us, 1536 = 48 MiB in 10 us
@@ -64,7 +68,7 @@ def test_summarize_floor_interpolates_the_read_floor(tmp_path):
         up = nb * 2 * cfg.H * cfg.I * esz
         for i in range(4):
             # gate/up at exactly 5 TB/s, down at 4 TB/s
-            rows.append(("void stmoe::(anonymous namespace)::ffn_gate_up<x>(stmoe::FfnArgs)", t, int(up / 5e3), 64))
+            rows.append((f"void stmoe::(anonymous namespace)::{up_kernel}<x>(stmoe::FfnArgs)", t, int(up / 5e3), 64))
             t += int(up / 5e3) + 10
             rows.append(("void stmoe::(anonymous namespace)::ffn_down_rows<x>(stmoe::FfnArgs)", t,
                          int(up / 2 / 4e3), 32))
@@ -76,7 +80,7 @@ def test_summarize_floor_interpolates_the_read_floor(tmp_path):
         bench.summarize_floor(str(rf), str(fs))
     txt = out.getvalue()
     assert "| 24 | 6.00 |" in txt and "| 48 | 10.00 |" in txt
-    gu = [l for l in txt.splitlines() if "`ffn_gate_up<x>`" in l]
+    gu = [l for l in txt.splitlines() if f"`{up_kernel}<x>`" in l]
     dn = [l for l in txt.splitlines() if "`ffn_down_rows<x>`" in l]
     assert len(gu) == len(dn) == len(bench.SWEEP_CONFIGS)
     for l in gu:       # GB/s from the algorithmic bytes (durations rounded to whole ns)
