@@ -1558,8 +1558,9 @@ Shape plan_shape(int B, int K, int H, int I, int E, int n_shared, int dtype) {
     // Which activations are held in bf16 is the same on every path: at batch 8
     // where the sizes are multiples of 64, else where the GEMV down kernel
     // takes them so.  bf16 shapes with fp32 activations keep the GEMV kernels
-    // (three bf16 operands per activation on the matrix cores summed to 5.0e-7
-    // of the 64-bit result, the GEMV to 3.1e-7).
+    // (three bf16 operands per activation on the matrix cores: relative L2 error
+    // 3.1e-7 against the 64-bit result at E 128 top-8 H 4096 I 1536, batch 4, where
+    // the GEMV kernels have 2.1e-7; at E 8 top-2 I 14336, batch 2, 5.0e-7 and 3.1e-7).
     const bool act16 = dtype == STMOE_BF16 && ((B == 8 && H % 64 == 0 && I % 64 == 0) || act_bf16<true>(s, B));
     // Two tokens, or up to four with fp32 weights and few long rows, keep the
     // GEMV kernels where their lane groups have no idle lanes and the tiles'
