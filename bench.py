@@ -300,7 +300,8 @@ def summarize_counters(fetch_csv, write_csv, meta_json):
 
 
 DECODE_KERNELS = ("route_logits_kernel", "route_tail_kernel", "route_plan_kernel", "route_update_predict_kernel",
-                  *UP_KERNELS, "ffn_down", "ffn_reduce", "update_predict", "decide_kernel", "blit_kernel", "set_table_kernel")
+                  *UP_KERNELS, "ffn_down", "ffn_reduce", "update_predict", "decide_kernel", "blit_kernel",
+                  "set_table_kernel")
 
 
 def summarize_gaps(trace_csv, title, cmd, skip_frac=0.25):

@@ -1455,7 +1455,7 @@ struct Shape {
     int dn_R;           // rows per lane group of the GEMV down kernel
 };
 
-constexpr int kUpSplitMaxBlocks = 640;        // 4-row gate/up: short rows are split up to this many workgroups unsplit
+constexpr int kUpSplitMaxBlocks = 640;        // 4-row gate/up: unsplit workgroups up to which short rows are split
 constexpr int kRoutePlanBlocks = 2048;        // 4-row gate/up workgroups beyond which the plan comes first (ffn_route_place)
 constexpr int kDownRowsWgTarget = 1024;  // lane-group down: fewest workgroups more rows per group may leave
 constexpr int kDownWgR = 4;   // rows per workgroup (whole-workgroup down)

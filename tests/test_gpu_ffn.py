@@ -254,12 +254,14 @@ def _ffn_launches(B, K, E, H, I, n_shared, dtype):
     y = torch.zeros((B, H), device=DEV)
     ws = torch.zeros(S.ffn_workspace_bytes(B, K, E, H, I, n_shared, sdt), dtype=torch.uint8, device=DEV)
     table, st = ptr_array([x.data_ptr()] * (E + n_shared)), torch.cuda.Stream()      # captured, not run
-    return graph_launches(lambda: S.expert_ffn(x, idx, w, H, I, E, sdt, table, y, ws, shared_ptrs=table if n_shared else None,
+    shared = table if n_shared else None
+    return graph_launches(lambda: S.expert_ffn(x, idx, w, H, I, E, sdt, table, y, ws, shared_ptrs=shared,
                                                n_shared=n_shared, stream=st), st)
 
 
 @pytest.mark.parametrize("B,K,E,H,I,n_shared,dtype,rows", [
-    (8, 8, 32, 1024, 1024, 0, "bf16", 16), (8, 4, 43, 1024, 1920, 0, "bf16", 16), (3, 6, 16, 1408, 4096, 1, "bf16", 16), (3, 6, 16, 1536, 1024, 1, "bf16", 4),
+    (8, 8, 32, 1024, 1024, 0, "bf16", 16), (8, 4, 43, 1024, 1920, 0, "bf16", 16),
+    (3, 6, 16, 1408, 4096, 1, "bf16", 16), (3, 6, 16, 1536, 1024, 1, "bf16", 4),
     (5, 4, 157, 640, 1152, 0, "f32", 16), (4, 6, 64, 2048, 1408, 2, "bf16", 4), (8, 5, 18, 1280, 400, 2, "bf16", 4),
     (8, 4, 8, 256, 64, 0, "bf16", 16),
 ])
