@@ -1355,7 +1355,9 @@ __global__ __launch_bounds__(kThreads) void ffn_down_mfma(FfnArgs a) {
         const char* wr[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) wr[t] = wd + size_t(h0 + t * 16 + n) * rowb;
-        const bool rt = LIST ? (p.tok[j] >> n) & 1u : arow;      // LIST: only routed tokens' activations exist
+        // only routed tokens' activations are read (the others are zero, or with
+        // LIST not written): E 43 top-3 + 2 H 2880 I 4032, batch 15, FFN 742 -> 656 us
+        const bool rt = (p.tok[j] >> n) & 1u;
         const char* ar = reinterpret_cast<const char*>(a.act) +
                          (size_t(j) * a.B + (arow ? n : 0)) * rowb + q * 16;
         auto step = [&](const bf16x8 (&w0)[NT], const bf16x8 (&w1)[NT], const bf16x8& a0, const bf16x8& a1) {
